@@ -21,6 +21,41 @@ struct qcd_point {
     double gs, gs2, gk;
 };
 
+// kappa (gk_of) and its powers (gkp_of) as the programs take them: of one
+// point's couplings C = Proc::coup<T>, or of M points side by side.
+template <typename T, typename C, int M>
+struct coup_m {
+    C v[M];
+};
+template <typename C> MGRW_HD auto gk_of(const C& c) { return c.gk; }
+template <typename C> MGRW_HD auto gkp_of(const C& c, int n) { return c.gkp[n]; }
+template <typename T, typename C, int M, int... m>
+MGRW_HD rm<T, M> gk_points(const coup_m<T, C, M>& c, std::integer_sequence<int, m...>) { return {{c.v[m].gk...}}; }
+template <typename T, typename C, int M, int... m>
+MGRW_HD rm<T, M> gkp_points(const coup_m<T, C, M>& c, int n, std::integer_sequence<int, m...>) {
+    return {{c.v[m].gkp[n]...}};
+}
+template <typename T, typename C, int M> MGRW_HD rm<T, M> gk_of(const coup_m<T, C, M>& c) {
+    return gk_points(c, points_seq<M>{});
+}
+template <typename T, typename C, int M> MGRW_HD rm<T, M> gkp_of(const coup_m<T, C, M>& c, int n) {
+    return gkp_points(c, n, points_seq<M>{});
+}
+// The couplings of points first .. first + M - 1 (places beyond the last point
+// repeat it).
+template <class Proc, typename T, int M, int... m>
+MGRW_HD auto couplings_seq(const qcd_point* pts, int first, int npts, std::integer_sequence<int, m...>) {
+    auto one = [&](int k) {
+        const qcd_point q = pts[k < npts ? k : npts - 1];
+        return Proc::template couplings<T>(q.gs, q.gs2, q.gk);
+    };
+    return coup_m<T, typename Proc::template coup<T>, M>{{one(first + m)...}};
+}
+template <class Proc, typename T, int M>
+MGRW_HD auto couplings_of(const qcd_point* pts, int first, int npts) {
+    return couplings_seq<Proc, T, M>(pts, first, npts, points_seq<M>{});
+}
+
 // |M|^2 of one event at one parameter point: the full amplitude program for
 // every helicity configuration, colour-summed, accumulated in double.
 // k and b are the event's kinematics and wavefunction bases, held in

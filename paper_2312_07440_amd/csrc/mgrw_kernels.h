@@ -231,8 +231,16 @@ template <class Proc, typename T>
 struct event_data {
     typename Proc::template kin<T> k;
     typename Proc::template basis<T> b;
+    typename Proc::template ext_table<T> t;
     int skip;   // 1: left to the FP64 re-evaluation
 };
+
+template <class Proc, typename T, typename P>
+__device__ __forceinline__ void fill_event(const P& p, double mt, event_data<Proc, T>& d) {
+    Proc::kinematics(p, mt, d.k);
+    Proc::external_basis(p, mt, d.b);
+    Proc::external_table(d.b, d.t);
+}
 
 // Kinematics and wavefunction bases of every event; with tau > 0 also lists
 // the ill-conditioned events (count, list) and marks them to be skipped.
@@ -248,8 +256,7 @@ qcd_setup_kernel(const double* __restrict__ mom, int64_t n, int64_t e0, int64_t 
     const int64_t e = e0 + el;
     double p[Proc::NEXT][4];
     load_event<Proc::NEXT>(mom, n, e, p);
-    Proc::kinematics(p, mt, ev[el].k);
-    Proc::external_basis(p, mt, ev[el].b);
+    fill_event(p, mt, ev[el]);
     int skip = 0;
     if (tau > 0.0 && ill_conditioned<Proc>(p, tau)) {
         skip = 1;
@@ -282,68 +289,248 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// Events e0 .. e0 + nb - 1 (record el = event e0 + el).
-template <class Proc, typename T>
-__global__ void __launch_bounds__(kBlock, MGRW_WAVE_WPE)
-qcd_wave_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t nb, const double* __restrict__ w_in,
-                int64_t n, qcd_launch a, double* __restrict__ out, double* __restrict__ me0_out) {
+// Points per pass of the one-event-per-wave kernels (and in double precision
+// the accumulators kept in LDS).  The Lorentz chains of a pass hold no
+// parameter and are formed once for its points; each point has its own
+// closures' couplings, flows, colour sum and helicity sum.  g g -> t tbar g g,
+// base + 16 points, amplitude kernel and re-evaluation, 2^20 events in single
+// and 20011 in double precision: one point a pass 272 ms and 12.5 ms; two
+// 190 ms, two with half of the first point's flows in LDS 213 ms (the LDS
+// read-modify-writes cost more than the 98 spilled registers they save), three
+// 262 ms (340 spilled); in double precision, bound by its 512 registers at one
+// wave per SIMD, two 7.9 ms, three 7.0 ms with 34 of the 72 accumulators in
+// LDS (7.8 with 26), four 8.9 ms.
+constexpr int kPointsF32 = 2, kPointsF64 = 3, kCellsF64 = 34;
+template <typename T, int M>
+struct pass_plan {
+    static constexpr int NL = sizeof(T) == 4 || M == 1 ? 0 : kCellsF64;
+};
+
+// A wave's share of LDS: the event's kinematics, its wavefunctions, and the
+// accumulators that the registers do not hold.
+template <class Proc, typename T, int M>
+struct wave_slot {
+    alignas(16) typename Proc::template kin<T> k;
+    alignas(16) typename Proc::template ext_table<T> t;
+    alignas(16) cx<T> j[64 * pass_plan<T, M>::NL + 1];
+};
+
+// M points of an event evaluated side by side: the flows' accumulators.
+// In single precision the first point's are an array, as in a program for one
+// point, and the further points' separate members, which are values from the
+// start and take no place in the basic block's order of loads and stores
+// (see rm).
+template <typename T, int K>
+struct flow_set {
+    flow_set<T, K - 1> lo;
+    cx<T> x = {T(0), T(0)};
+    template <int I>
+    __device__ __forceinline__ cx<T>& at() {
+        if constexpr (I == K - 1)
+            return x;
+        else
+            return lo.template at<I>();
+    }
+};
+template <typename T>
+struct flow_set<T, 0> {};
+template <typename T, int K, int M>
+struct point_acc {
+    cx<T> J[K];
+    flow_set<T, K> more[M > 1 ? M - 1 : 1];
+    __device__ __forceinline__ void clear() {
+        for (int i = 0; i < K; ++i) J[i] = {T(0), T(0)};
+    }
+};
+template <int I, typename T, int K, int M, int... m>
+__device__ __forceinline__ void jadd_more(point_acc<T, K, M>& J, const cm<T, M>& s, std::integer_sequence<int, m...>) {
+    ((J.more[m].template at<I>() = J.more[m].template at<I>() + s.v[m + 1]), ...);
+}
+template <int I, typename T, int K, int M, int... m>
+__device__ __forceinline__ void jsub_more(point_acc<T, K, M>& J, const cm<T, M>& s, std::integer_sequence<int, m...>) {
+    ((J.more[m].template at<I>() = J.more[m].template at<I>() - s.v[m + 1]), ...);
+}
+template <int I, typename T, int K, int M>
+__device__ __forceinline__ void jadd(point_acc<T, K, M>& J, const cm<T, M>& s) {
+    J.J[I] = J.J[I] + s.v[0];
+    jadd_more<I>(J, s, points_seq<M - 1>{});
+}
+template <int I, typename T, int K, int M>
+__device__ __forceinline__ void jsub(point_acc<T, K, M>& J, const cm<T, M>& s) {
+    J.J[I] = J.J[I] - s.v[0];
+    jsub_more<I>(J, s, points_seq<M - 1>{});
+}
+template <int I, typename T, int K, int KK>
+__device__ __forceinline__ void flows_out(flow_set<T, K>& x, cx<T> (&J)[KK]) {
+    if constexpr (I < KK) {
+        J[I] = x.template at<I>();
+        flows_out<I + 1>(x, J);
+    }
+}
+template <class Proc, typename T, int K, int M>
+__device__ __forceinline__ void colour_points(point_acc<T, K, M>& J, double (&acc)[M]) {
+    acc[0] += double(Proc::colour_sum(J.J));
+#pragma unroll
+    for (int m = 1; m < M; ++m) {
+        cx<T> Jm[K];
+        flows_out<0>(J.more[m - 1], Jm);
+        acc[m] += double(Proc::colour_sum(Jm));
+    }
+}
+
+// In double precision: entry q = m K + i (flow i of point m), the first NL of
+// them in the lane's LDS column (entry q at lds[64 q]) and the others in
+// registers.  The program's indices are constants, so each access resolves to
+// one storage at compile time.
+template <int K, int M, int NL>
+struct point_cells {
+    cx<double>* lds;
+    cx<double> reg[M * K - NL];
+    __device__ __forceinline__ cx<double>& at(int q) { return q < NL ? lds[64 * q] : reg[q - NL]; }
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int q = 0; q < M * K; ++q) at(q) = {0.0, 0.0};
+    }
+};
+template <int I, int K, int M, int NL>
+__device__ __forceinline__ void jadd(point_cells<K, M, NL>& J, const cm<double, M>& s) {
+#pragma unroll
+    for (int m = 0; m < M; ++m) J.at(m * K + I) = J.at(m * K + I) + s.v[m];
+}
+template <int I, int K, int M, int NL>
+__device__ __forceinline__ void jsub(point_cells<K, M, NL>& J, const cm<double, M>& s) {
+#pragma unroll
+    for (int m = 0; m < M; ++m) J.at(m * K + I) = J.at(m * K + I) - s.v[m];
+}
+template <class Proc, int K, int M, int NL>
+__device__ __forceinline__ void colour_points(point_cells<K, M, NL>& J, double (&acc)[M]) {
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        cx<double> Jm[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) Jm[i] = J.at(m * K + i);
+        acc[m] += Proc::colour_sum(Jm);
+    }
+}
+
+template <class Proc, typename T, typename W, typename KN, typename C, typename JA>
+__device__ __forceinline__ void amplitude_points(const W& w, const KN& k, const C& c, JA& J) {
+    J.clear();
+    Proc::template program<T>(w, k, c, J);
+}
+
+// |M|^2 of one event at points first .. first + M - 1 (of npts), summed over
+// the helicity configurations on the wave's lanes; the same value in every
+// lane.  s.k and s.t hold the event.
+template <class Proc, typename T, int M>
+__device__ __forceinline__ void pass_me(wave_slot<Proc, T, M>& s, const qcd_launch& a, int first, int lane,
+                                        double (&me)[M]) {
+    constexpr int K = Proc::K;
+    const auto c = couplings_of<Proc, T, M>(a.pts, first, a.npts);
+    double acc[M] = {};
+#pragma unroll 1
+    for (int hc = 0; hc < Proc::NHEL; hc += 64) {
+        __asm__ volatile("" ::: "memory");
+        const auto w = Proc::template ext_at<T>(s.t, hc + lane);
+        if constexpr (sizeof(T) == 4) {
+            point_acc<T, K, M> J;
+            amplitude_points<Proc, T>(w, lds_near_use(s.k), c, J);
+            colour_points<Proc>(J, acc);
+        } else {
+            point_cells<K, M, pass_plan<T, M>::NL> J{&s.j[lane], {}};
+            amplitude_points<Proc, T>(w, lds_near_use(s.k), c, J);
+            colour_points<Proc>(J, acc);
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+        me[m] = wave_sum(acc[m]) * Proc::point_norm(a.pts[first + m < a.npts ? first + m : a.npts - 1].gs);
+}
+
+// |M|^2 of point kp of event e: the base point's to me0[i], a new point's to
+// its place in out, where reweight_ratio_kernel replaces it by the weight.
+__device__ __forceinline__ void store_me(double me, int kp, int64_t e, int64_t i, int64_t n, const qcd_launch& a,
+                                         double* __restrict__ out, double* __restrict__ me0) {
+    if (kp >= a.npts) return;
+    if (kp > 0)
+        out[int64_t(kp - 1) * n + e] = me;
+    else if (a.mode == 1)
+        out[e] = me;
+    else
+        me0[i] = me;
+}
+
+// Eq. (3) for events e0 .. e0 + nb - 1 once their |M|^2 are in out and me0
+// (w[i], me0[i]: input weight, if any, and base point of event e0 + i); grid
+// (events, new points).
+template <int BLOCK>
+__global__ void __launch_bounds__(BLOCK)
+reweight_ratio_kernel(const double* w, const double* me0, int64_t e0, int64_t nb, int64_t n, double* out) {
+    const int64_t i = int64_t(blockIdx.x) * BLOCK + threadIdx.x;
+    if (i >= nb) return;
+    const int64_t at = int64_t(blockIdx.y) * n + e0 + i;
+    out[at] = reweighted(w ? w[i] : 1.0, out[at], me0[i]);
+}
+
+// Input weights set aside where out or me0 overlap them: |M|^2 is written there
+// before the weights are read.
+template <int BLOCK>
+__global__ void __launch_bounds__(BLOCK) copy_weights_kernel(const double* w, int64_t nb, double* to) {
+    const int64_t i = int64_t(blockIdx.x) * BLOCK + threadIdx.x;
+    if (i < nb) to[i] = w[i];
+}
+inline bool overlap(const double* a, int64_t na, const double* b, int64_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && x < y + 8 * uintptr_t(nb) && y < x + 8 * uintptr_t(na);
+}
+
+// Events from which on a unit of work is a whole event; below, one pass, so
+// that a small batch fills the chip (2048 waves in single precision, 1024 in
+// double).  1000 events x 17 points: 305 us against 1150 with whole events;
+// at 33000 events units of one pass still gain 1 %, at 65536 and above whole
+// events, which stage their record once, are 2-4 % faster.
+constexpr int64_t kWholeEvents = 16384;
+
+// One wave's unit of work: event e0 + el, passes [u per, (u + 1) per) over its
+// points, M points a pass.  Bound by VALU issue: a wave issues at most one
+// vector instruction per four cycles and a SIMD takes two, so two waves per
+// SIMD (256 registers) are needed and one runs at half rate.
+template <class Proc, typename T, int M>
+__global__ void __launch_bounds__(kBlock, sizeof(T) == 4 ? MGRW_WAVE_WPE : 1)
+qcd_wave_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t nb, int64_t n, int units, int per,
+                qcd_launch a, double* __restrict__ out, double* __restrict__ me0) {
     static_assert(Proc::NHEL % 64 == 0, "helicity configurations must fill whole waves");
-    const int64_t el = int64_t(blockIdx.x) * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (el >= nb || ev[el].skip) return;   // whole wave; no barriers below
-    const int64_t e = e0 + el;
-    const int lane = threadIdx.x & 63;
-    // the event's kinematics record, staged once per event in LDS (one record
-    // per wave): the program reads it with broadcast LDS loads
-    using KIN = typename Proc::template kin<T>;
-    struct alignas(16) kin_slot { KIN v; };
-    static_assert(sizeof(KIN) % 4 == 0, "record copied in 32-bit words");
-    __shared__ kin_slot kl[kBlock / 64];
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t id = int64_t(blockIdx.x) * (kBlock / 64) + wv;
+    const int64_t el = id / units;
+    if (el >= nb || ev[el].skip) return;   // whole wave; no barriers below
+    const int lane = threadIdx.x & 63;
+    // the event's record, staged once per unit in LDS: the program reads the
+    // kinematics with broadcast loads, the wavefunctions at the lane's
+    // helicities
+    using S = wave_slot<Proc, T, M>;
+    __shared__ S sl[kBlock / 64];
+    S& s = sl[wv];
     {
+        static_assert(sizeof(s.k) % 4 == 0 && sizeof(s.t) % 4 == 0, "record copied in 32-bit words");
         const uint32_t* src = reinterpret_cast<const uint32_t*>(&ev[el].k);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(&kl[wv].v);
-        for (int i = lane; i < int(sizeof(KIN) / 4); i += 64) dst[i] = src[i];
+        uint32_t* dst = reinterpret_cast<uint32_t*>(&s.k);
+        for (int i = lane; i < int(sizeof(s.k) / 4); i += 64) dst[i] = src[i];
+        src = reinterpret_cast<const uint32_t*>(&ev[el].t);
+        dst = reinterpret_cast<uint32_t*>(&s.t);
+        for (int i = lane; i < int(sizeof(s.t) / 4); i += 64) dst[i] = src[i];
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    const KIN& k = kl[wv].v;
-    const typename Proc::template basis<T>& b = ev[el].b;
-    const double w = (a.mode == 0 && w_in) ? w_in[e] : 1.0;
-    // the lane's external wavefunctions live in its own LDS slot: they are
-    // read throughout the program, and in registers they push the program's
-    // working set into scratch.  With one block of 64 configurations they do
-    // not depend on the point and are assembled once per event.
-    __shared__ lds_slot<typename Proc::template ext<T>> wfs[kBlock];
-    typename Proc::template ext<T>& wf = wfs[threadIdx.x].v;
-    constexpr bool one_block = Proc::NHEL == 64;
-    if constexpr (one_block) Proc::template external<T>(b, lane, wf);
-    double me0 = 0.0;
+    const int k0 = int(id - el * units) * per * M, k1 = k0 + per * M < a.npts ? k0 + per * M : a.npts;
 #pragma unroll 1
-    for (int kp = 0; kp < a.npts; ++kp) {
-        const qcd_point pt = a.pts[kp];
-        const auto c = Proc::template couplings<T>(pt.gs, pt.gs2, pt.gk);
-        double acc = 0.0;
-#pragma unroll 1
-        for (int hc = 0; hc < Proc::NHEL; hc += 64) {
-            __asm__ volatile("" ::: "memory");
-            if constexpr (!one_block) Proc::template external<T>(b, hc + lane, wf);
-            cx<T> J[Proc::K];
-            Proc::amplitude(wf, lds_near_use(k), c, J);
-            acc += double(Proc::colour_sum(J));
-        }
-        const double me = wave_sum(acc) * Proc::point_norm(pt.gs);
-        if (kp == 0) {
-            me0 = me;
-            if (lane == 0) {
-                if (a.mode == 1)
-                    out[e] = me;
-                else if (me0_out)
-                    me0_out[e] = me;
-            }
-        } else if (lane == 0) {
-            out[int64_t(kp - 1) * n + e] = reweighted(w, me, me0);
-        }
+    for (int kp = k0; kp < k1; kp += M) {
+        double me[M];
+        pass_me<Proc, T, M>(s, a, kp, lane, me);
+        if (lane == 0)
+#pragma unroll
+            for (int m = 0; m < M; ++m) store_me(me[m], kp + m, e0 + el, el, n, a, out, me0);
     }
 }
 
@@ -548,6 +735,52 @@ qcd_rescue_kernel(const double* __restrict__ mom, const int64_t* __restrict__ li
     }
 }
 
+// The same for the one-event-per-wave pipeline: M points a pass, the listed
+// events' points split over waves while the list is short (a unit is then one
+// pass), |M|^2 to out and me0 (of event e: me0[e - e0]).
+template <class Proc, int M>
+__global__ void __launch_bounds__(kBlock, 1)
+qcd_redo_kernel(const double* __restrict__ mom, const int64_t* __restrict__ list,
+                const unsigned long long* __restrict__ count, int64_t n, int64_t e0, qcd_launch a,
+                double* __restrict__ out, double* __restrict__ me0) {
+    __shared__ wave_slot<Proc, double, M> sl[kBlock / 64];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int64_t cnt = int64_t(count[0]);
+    const int64_t stride = int64_t(gridDim.x) * (kBlock / 64);
+    const int passes = (a.npts + M - 1) / M;
+    const int units = cnt < kWholeEvents ? passes : 1, per = passes / units;
+    wave_slot<Proc, double, M>& s = sl[wv];
+#pragma unroll 1
+    for (int64_t id = int64_t(blockIdx.x) * (kBlock / 64) + wv; id < cnt * units; id += stride) {
+        const int64_t i = id / units;
+        const int64_t e = list[i];
+        if (lane == 0) {
+            double p[Proc::NEXT][4];
+            load_event<Proc::NEXT>(mom, n, e, p);
+            typename Proc::template basis<double> b;
+            Proc::kinematics(p, a.mt, s.k);
+            Proc::external_basis(p, a.mt, b);
+            Proc::external_table(b, s.t);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int k0 = int(id - i * units) * per * M, k1 = k0 + per * M < a.npts ? k0 + per * M : a.npts;
+#pragma unroll 1
+        for (int kp = k0; kp < k1; kp += M) {
+            double me[M];
+            pass_me<Proc, double, M>(s, a, kp, lane, me);
+            if (lane == 0)
+#pragma unroll
+                for (int m = 0; m < M; ++m) store_me(me[m], kp + m, e, e - e0, n, a, out, me0);
+        }
+        // every lane has read the slot before the next event overwrites it
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 constexpr unsigned kRescueBlocks = 1024;
 
 // The FP64 re-evaluation after a one-event-per-lane pass: list the
@@ -590,66 +823,100 @@ hipError_t launch_rescue(const double* mom, const double* w_in, int64_t n, const
     }
 }
 
+// |M|^2 of events e0 .. e0 + nb - 1 from their records, M points a pass, then
+// (list non-null) of the listed ones again in double precision.
+template <class Proc, typename T, int M>
+void launch_passes(const event_data<Proc, T>* ev, const double* mom, int64_t n, int64_t e0, int64_t nb,
+                   const int64_t* list, const unsigned long long* count, const qcd_launch& a, double* out,
+                   double* me0, hipStream_t s) {
+    const int passes = (a.npts + M - 1) / M;
+    const int units = nb < kWholeEvents ? passes : 1, per = passes / units;
+    mark(a.t0, s);
+    hipLaunchKernelGGL((qcd_wave_kernel<Proc, T, M>), dim3(unsigned((nb * units + kBlock / 64 - 1) / (kBlock / 64))),
+                       dim3(kBlock), 0, s, ev, e0, nb, n, units, per, a, out, me0);
+    mark(a.t1, s);
+    if constexpr (sizeof(T) == 4)
+        if (list)
+            hipLaunchKernelGGL((qcd_redo_kernel<Proc, M == 1 ? 1 : kPointsF64>), dim3(kRescueBlocks), dim3(kBlock), 0, s, mom, list, count,
+                               n, e0, a, out, me0);
+}
+
 // One event per wave: per-event data (in single precision with the rescue
 // on, also the list of ill-conditioned events, which the amplitude kernel
-// skips), the amplitude kernel, then the FP64 re-evaluation of the listed
-// events.  KP: kappa-polynomial evaluation.  Without a scratch span the
-// buffers are stream-ordered allocations for all n events; with one they are
-// carved from it (records, then count and list) and the events run in chunks
-// whose buffers fit.
+// skips), the amplitude kernel, the FP64 re-evaluation of the listed events,
+// then (plain evaluation) the weights from |M|^2.  KP: kappa-polynomial
+// evaluation.  Without a scratch span the buffers are one stream-ordered
+// allocation for all n events; with one they are carved from it and the events
+// run in chunks whose buffers fit.  Buffers: records, count and list, |M|^2 at
+// the base point (where the caller does not want it), input weights set aside.
 template <class Proc, typename T, bool KP>
 hipError_t launch_wave_pipeline(const double* mom, const double* w_in, int64_t n, const qcd_launch& a, double* out,
                                 double* me0, hipStream_t s) {
     const bool rescue = sizeof(T) == 4 && a.rescue_tau > 0.0 && Proc::NEXT > 4;
+    const bool base = !KP && a.mode == 0 && !me0;   // room for |M|^2 at the base point
     using ED = event_data<Proc, T>;
-    ED* ev = nullptr;
-    int64_t* buf = nullptr;
+    // room for the input weights, where the outputs overlap them
+    const bool aside = !KP && a.mode == 0 && (overlap(w_in, n, out, (a.npts - 1) * n) || overlap(w_in, n, me0, n));
+    const size_t words = (rescue ? 1 : 0) + (base ? 1 : 0) + (aside ? 1 : 0);
     int64_t chunk = n;
-    if (a.scratch.ptr) {
-        // per event: one record and (rescue) one list entry; head: the count
-        // word and the alignment of the list
-        chunk = scratch_chunk(a.scratch, sizeof(ED) + (rescue ? sizeof(int64_t) : 0), 512);
+    char* mem = static_cast<char*>(a.scratch.ptr);
+    if (mem) {
+        chunk = scratch_chunk(a.scratch, sizeof(ED) + words * 8, 1536);
         if (chunk < 1) return hipErrorInvalidValue;
-        ev = static_cast<ED*>(a.scratch.ptr);
-        if (rescue)
-            buf = reinterpret_cast<int64_t*>(static_cast<char*>(a.scratch.ptr) + align256(sizeof(ED) * size_t(chunk)));
+        if (chunk > n) chunk = n;
     } else {
-        hipError_t err = hipMallocAsync(reinterpret_cast<void**>(&ev), sizeof(ED) * size_t(n), s);
+        hipError_t err = hipMallocAsync(reinterpret_cast<void**>(&mem), align256(sizeof(ED) * size_t(n)) + 512 +
+                                        words * align256(8 * size_t(n)), s);
         if (err != hipSuccess) return err;
-        if (rescue) {
-            err = hipMallocAsync(reinterpret_cast<void**>(&buf), sizeof(int64_t) * size_t(n + 1), s);
-            if (err != hipSuccess) {
-                (void)hipFreeAsync(ev, s);
-                return err;
-            }
-        }
     }
-    unsigned long long* count = rescue ? reinterpret_cast<unsigned long long*>(buf) : nullptr;
-    int64_t* list = rescue ? buf + 1 : nullptr;
+    ED* ev = reinterpret_cast<ED*>(mem);
+    char* at = mem + align256(sizeof(ED) * size_t(chunk));
+    unsigned long long* count = nullptr;
+    int64_t* list = nullptr;
+    if (rescue) {
+        count = reinterpret_cast<unsigned long long*>(at);
+        list = reinterpret_cast<int64_t*>(at + 256);
+        at += 256 + align256(8 * size_t(chunk));
+    }
+    double* m0_buf = reinterpret_cast<double*>(at);
+    if (base) at += align256(8 * size_t(chunk));
+    double* w_buf = reinterpret_cast<double*>(at);
     hipError_t err = hipSuccess;
     for (int64_t e0 = 0; e0 < n && err == hipSuccess; e0 += chunk) {
         const int64_t nb = n - e0 < chunk ? n - e0 : chunk;
         if (rescue) hipLaunchKernelGGL((rescue_reset_kernel<Proc>), dim3(1), dim3(64), 0, s, count);
         hipLaunchKernelGGL((qcd_setup_kernel<Proc, T>), dim3(unsigned((nb + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                            s, mom, n, e0, nb, a.mt, ev, rescue ? a.rescue_tau : 0.0, count, list);
-        const dim3 grid(unsigned((nb + kBlock / 64 - 1) / (kBlock / 64)));
-        mark(a.t0, s);
-        if constexpr (KP)
-            hipLaunchKernelGGL((qcd_kpoly_wave_kernel<Proc, T>), grid, dim3(kBlock), 0, s, ev, e0, nb, w_in, n, a,
-                               out, me0);
-        else
-            hipLaunchKernelGGL((qcd_wave_kernel<Proc, T>), grid, dim3(kBlock), 0, s, ev, e0, nb, w_in, n, a, out,
-                               me0);
-        mark(a.t1, s);
-        if (rescue)
-            hipLaunchKernelGGL((qcd_rescue_kernel<Proc, KP>), dim3(kRescueBlocks), dim3(kBlock), 0, s, mom, list,
-                               count, w_in, n, a, out, me0);
+        if constexpr (KP) {
+            mark(a.t0, s);
+            hipLaunchKernelGGL((qcd_kpoly_wave_kernel<Proc, T>), dim3(unsigned((nb + kBlock / 64 - 1) / (kBlock / 64))),
+                               dim3(kBlock), 0, s, ev, e0, nb, w_in, n, a, out, me0);
+            mark(a.t1, s);
+            if (rescue)
+                hipLaunchKernelGGL((qcd_rescue_kernel<Proc, KP>), dim3(kRescueBlocks), dim3(kBlock), 0, s, mom, list,
+                                   count, w_in, n, a, out, me0);
+        } else {
+            double* m0 = base ? m0_buf : (me0 ? me0 + e0 : nullptr);
+            const double* w = w_in ? w_in + e0 : nullptr;
+            const unsigned blocks = unsigned((nb + kBlock - 1) / kBlock);
+            if (aside) {
+                hipLaunchKernelGGL((copy_weights_kernel<kBlock>), dim3(blocks), dim3(kBlock), 0, s, w, nb, w_buf);
+                w = w_buf;
+            }
+            constexpr int M = sizeof(T) == 4 ? kPointsF32 : kPointsF64;
+            if (a.npts > 1)
+                launch_passes<Proc, T, M>(ev, mom, n, e0, nb, list, count, a, out, m0, s);
+            else
+                launch_passes<Proc, T, 1>(ev, mom, n, e0, nb, list, count, a, out, m0, s);
+            if (a.mode == 0 && a.npts > 1)
+                hipLaunchKernelGGL((reweight_ratio_kernel<kBlock>), dim3(blocks, unsigned(a.npts - 1)), dim3(kBlock),
+                                   0, s, w, m0, e0, nb, n, out);
+        }
         err = hipGetLastError();
     }
     if (a.scratch.ptr) return err;
-    hipError_t f1 = rescue ? hipFreeAsync(buf, s) : hipSuccess;
-    hipError_t f2 = hipFreeAsync(ev, s);
-    return err != hipSuccess ? err : (f1 != hipSuccess ? f1 : f2);
+    hipError_t ferr = hipFreeAsync(mem, s);
+    return err != hipSuccess ? err : ferr;
 }
 
 template <class Proc, typename T>
@@ -726,7 +993,7 @@ qcd_part_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t 
 #pragma unroll
                 for (int f = 0; f < Proc::K; ++f) J[f] = {jp[(2 * f) * NH], jp[(2 * f + 1) * NH]};
             }
-            Proc::template amplitude_part<C>(wf, k, c, J);
+            Proc::template amplitude_part<C, T>(wf, k, c, J);
             if constexpr (!LAST) {
 #pragma unroll
                 for (int f = 0; f < Proc::K; ++f) {
@@ -928,8 +1195,7 @@ qcd_setup64_kernel(const double* __restrict__ mom, int64_t n, double mt, const i
     const int64_t e = list ? list[i] : i;
     double p[Proc::NEXT][4];
     load_event<Proc::NEXT>(mom, n, e, p);
-    Proc::kinematics(p, mt, ev[i].k);
-    Proc::external_basis(p, mt, ev[i].b);
+    fill_event(p, mt, ev[i]);
     ev[i].skip = 0;
 }
 
@@ -965,7 +1231,7 @@ qcd_fr_kernel(const event_data<Proc, double>* __restrict__ ev, const unsigned lo
 #pragma unroll
                 for (int f = 0; f < KR; ++f) J[f] = {jp[(2 * f) * NH], jp[(2 * f + 1) * NH]};
             }
-            Proc::template amplitude_fr<C, R>(wf, k, c, J);
+            Proc::template amplitude_fr<C, R, double>(wf, k, c, J);
 #pragma unroll
             for (int f = 0; f < KR; ++f) {
                 jp[(2 * f) * NH] = J[f].re;

@@ -17,6 +17,8 @@
 #pragma once
 
 #include <cmath>
+#include <type_traits>
+#include <utility>
 
 #if defined(__HIPCC__)
 #include <hip/hip_runtime.h>
@@ -85,6 +87,53 @@ template <typename T> MGRW_HD cx<T> cmad(cx<T> a, cx<T> b, zero) { return a * b;
 template <typename T> MGRW_HD cx<T> cmsb(cx<T> a, cx<T> b, zero) { return -(a * b); }
 template <typename T, typename Acc> MGRW_HD Acc cmad(zero, cx<T>, Acc acc) { return acc; }
 template <typename T, typename Acc> MGRW_HD Acc cmsb(zero, cx<T>, Acc acc) { return acc; }
+
+// --- values of M parameter points side by side ---
+// A program evaluated for M points at once holds one Lorentz chain (no
+// parameter enters it) and, from the closures on, one value per point.
+// Written out by pack expansion, not as loops: the compiler orders the operands
+// of a sum by their places in the basic block, and the order decides which of
+// two products a fused multiply-add takes.  Straight-line code in which every
+// point has the same depth of calls leaves each point's rounding as it is in
+// the program for one point.
+template <typename T, int M>
+struct rm {
+    T v[M];
+};
+template <typename T, int M>
+struct cm {
+    cx<T> v[M];
+};
+template <int M> using points_seq = std::make_integer_sequence<int, M>;
+template <typename T, int M, int... m>
+MGRW_HD cm<T, M> mul_points(cx<T> x, const rm<T, M>& f, std::integer_sequence<int, m...>) { return {{(x * f.v[m])...}}; }
+template <typename T, int M, int... m>
+MGRW_HD cm<T, M> add_points(const cm<T, M>& x, const cm<T, M>& y, std::integer_sequence<int, m...>) {
+    return {{(x.v[m] + y.v[m])...}};
+}
+template <typename T, int M, int... m>
+MGRW_HD cm<T, M> sub_points(const cm<T, M>& x, const cm<T, M>& y, std::integer_sequence<int, m...>) {
+    return {{(x.v[m] - y.v[m])...}};
+}
+template <typename T, int M, int... m>
+MGRW_HD cm<T, M> neg_points(const cm<T, M>& x, std::integer_sequence<int, m...>) { return {{(-x.v[m])...}}; }
+template <typename T, int M> MGRW_HD cm<T, M> operator*(cx<T> x, const rm<T, M>& f) {
+    return mul_points(x, f, points_seq<M>{});
+}
+template <typename T, int M> MGRW_HD cm<T, M> operator+(const cm<T, M>& x, const cm<T, M>& y) {
+    return add_points(x, y, points_seq<M>{});
+}
+template <typename T, int M> MGRW_HD cm<T, M> operator-(const cm<T, M>& x, const cm<T, M>& y) {
+    return sub_points(x, y, points_seq<M>{});
+}
+template <typename T, int M> MGRW_HD cm<T, M> operator-(const cm<T, M>& x) { return neg_points(x, points_seq<M>{}); }
+
+// Add to / subtract from colour-flow accumulator I.  J: a pointer or array of
+// one point's flows, or an object with jadd<I> of its own (several points).
+template <int I, typename JA, typename T>
+MGRW_HD void jadd(JA&& J, const cx<T>& s) { J[I] = J[I] + s; }
+template <int I, typename JA, typename T>
+MGRW_HD void jsub(JA&& J, const cx<T>& s) { J[I] = J[I] - s; }
 
 // --- four-vectors ---
 template <typename T>
@@ -347,15 +396,16 @@ MGRW_HD sp<T> ffv_col(const v4<T, A>& J, const sp<T>& v, const r4<T>& q, T m, T 
     return ffv_col(J, v, lc4_of(q), m, coup);
 }
 
-// Closing vertex: coup * a . Jslash . v, coup = g kappa.
-template <typename T, typename A>
-MGRW_HD cx<T> ffv_amp(const sp<T>& a, const v4<T, A>& J, const sp<T>& v, T coup) {
+// Closing vertex: coup * a . Jslash . v, coup = g kappa (of one point, or of
+// several: then one value per point).
+template <typename T, typename A, typename C>
+MGRW_HD auto ffv_amp(const sp<T>& a, const v4<T, A>& J, const sp<T>& v, const C& coup) {
     return row_col(row_slash(a, J), v) * coup;
 }
 // The same closure associated as a . (Jslash . v): it then shares Jslash . v
 // with the column current that continues through this vertex.
-template <typename T, typename A>
-MGRW_HD cx<T> ffv_amp_col(const sp<T>& a, const v4<T, A>& J, const sp<T>& v, T coup) {
+template <typename T, typename A, typename C>
+MGRW_HD auto ffv_amp_col(const sp<T>& a, const v4<T, A>& J, const sp<T>& v, const C& coup) {
     return row_col(a, slash_col(J, v)) * coup;
 }
 
@@ -371,13 +421,79 @@ MGRW_HD v4<T> vector_current(const sp<T>& a, const sp<T>& b) {
     return j;
 }
 
-// The t tbar current f * (ubar gamma^mu v): the off-shell gluon emitted by the
-// top line with no other attachment (f carries g kappa and 1/P^2).
+// The t tbar current coup * iP * (ubar gamma^mu v): the off-shell gluon emitted
+// by the top line with no other attachment (coup = g kappa, iP = 1/P^2).
 template <typename T>
-MGRW_HD v4<T> tt_current(const sp<T>& ub, const sp<T>& v, T f) {
+MGRW_HD v4<T> tt_current(const sp<T>& ub, const sp<T>& v, T coup, T iP) {
+    const T f = coup * iP;
     v4<T> j = vector_current(ub, v);
     return {j.t * f, j.x * f, j.y * f, j.z * f};
 }
+
+// The same for M points.  In single precision each point has its own scaled
+// current, so that its root closures round as they do for one point alone;
+// in double precision the points share the current without their coupling,
+// which multiplies the closed vertex instead.
+template <int M>
+struct ttk {
+    v4<float> v[M];
+};
+template <int M>
+struct ttk_shared {
+    v4<double> v;
+    rm<double, M> coup;
+};
+template <int M, int... m>
+MGRW_HD ttk<M> tt_points(const sp<float>& ub, const sp<float>& v, const rm<float, M>& coup, float iP,
+                         std::integer_sequence<int, m...>) {
+    return {{tt_current(ub, v, coup.v[m], iP)...}};
+}
+template <int M>
+MGRW_HD ttk<M> tt_current(const sp<float>& ub, const sp<float>& v, const rm<float, M>& coup, float iP) {
+    return tt_points(ub, v, coup, iP, points_seq<M>{});
+}
+template <int M>
+MGRW_HD ttk_shared<M> tt_current(const sp<double>& ub, const sp<double>& v, const rm<double, M>& coup, double iP) {
+    return {tt_current(ub, v, 1.0, iP), coup};
+}
+
+// Root closures on the t tbar current K of one point or of M points (at most
+// two in single precision): macros, so that every point's closure is a call
+// in the program itself and rounds as in the program for one point (see rm).
+template <typename T> MGRW_HD const v4<T>& root_at(const v4<T>& K, int) { return K; }
+template <int M> MGRW_HD const v4<float>& root_at(const ttk<M>& K, int m) { return K.v[m]; }
+template <int M> MGRW_HD const v4<double>& root_at(const ttk_shared<M>& K, int) { return K.v; }
+template <typename K> struct root_points { static constexpr int n = 1; };
+template <int M> struct root_points<const ttk<M>> { static constexpr int n = M; };
+template <typename T> MGRW_HD cx<T> root_value(const v4<T>&) { return {}; }
+template <int M> MGRW_HD cm<float, M> root_value(const ttk<M>&) { return {}; }
+template <int M> MGRW_HD cx<double> root_value(const ttk_shared<M>&) { return {}; }
+template <typename T> MGRW_HD void root_put(cx<T>& a, int, cx<T> x) { a = x; }
+template <typename T, int M> MGRW_HD void root_put(cm<T, M>& a, int m, cx<T> x) { a.v[m] = x; }
+template <typename T> MGRW_HD cx<T> root_done(const v4<T>&, cx<T> a) { return a; }
+template <int M> MGRW_HD const cm<float, M>& root_done(const ttk<M>&, const cm<float, M>& a) { return a; }
+template <int M> MGRW_HD cm<double, M> root_done(const ttk_shared<M>& K, cx<double> a) { return a * K.coup; }
+template <typename V>
+struct root_parts {
+    V A, B, C;
+};
+template <typename V, typename T>
+MGRW_HD void root_put(root_parts<V>& r, int m, const vvvv_closed<T>& q) {
+    root_put(r.A, m, q.A);
+    root_put(r.B, m, q.B);
+    root_put(r.C, m, q.C);
+}
+#define MGRW_CLOSE_V3(name, K, J1, J2, V)                                                             \
+    auto name##_ = root_value(K);                                                                     \
+    root_put(name##_, 0, vvv_close(root_at(K, 0), J1, J2, V));                                        \
+    if constexpr (root_points<decltype(K)>::n > 1) root_put(name##_, 1, vvv_close(root_at(K, 1), J1, J2, V)); \
+    const auto name = root_done(K, name##_);
+#define MGRW_CLOSE_V4(name, K, J1, J2, J3)                                                            \
+    root_parts<decltype(root_value(K))> name##_;                                                      \
+    root_put(name##_, 0, vvvv_close(root_at(K, 0), J1, J2, J3));                                      \
+    if constexpr (root_points<decltype(K)>::n > 1) root_put(name##_, 1, vvvv_close(root_at(K, 1), J1, J2, J3)); \
+    const root_parts<std::decay_t<decltype(root_done(K, name##_.A))>> name = {root_done(K, name##_.A), root_done(K, name##_.B), \
+                                                                root_done(K, name##_.C)};
 
 // ------------------------------------------------ external wavefunctions
 

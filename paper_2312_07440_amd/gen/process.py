@@ -443,7 +443,7 @@ class Emitter:
         if v:
             return v
         self.iP_needed.add(self.full)
-        self.emit(f"const v4<T> jtt = tt_current(w.ub, w.v, c.gk * k.iP{self.full});")
+        self.emit(f"const auto jtt = tt_current(w.ub, w.v, gk_of(c), k.iP{self.full});")
         self.counts["tt_current"] += 1
         self.global_cache["Jtt"] = "jtt"
         return "jtt"
@@ -476,20 +476,19 @@ class Emitter:
             if name is None:
                 name = self.var("s")
                 self.pending[key] = name
-                self.emit(f"cx<T> {name} = {'' if s0 > 0 else '-'}{amp};")
+                self.emit(f"auto {name} = {'' if s0 > 0 else '-'}{amp};")
             else:
                 self.emit(f"{name} = {name} {'+' if s0 > 0 else '-'} {amp};")
             return
         for j, c in terms:
-            op = "+" if c > 0 else "-"
-            self.emit(f"J[{j}] = J[{j}] {op} {amp};")
+            self.emit(f"{'jadd' if c > 0 else 'jsub'}<{j}>(J, {amp});")
             self.n_jterms += 1
 
     def flush(self):
         """Add the group's pattern sums to their flows."""
         for key, name in self.pending.items():
             for j, c in key:
-                self.emit(f"J[{j}] = J[{j}] {'+' if c > 0 else '-'} {name};")
+                self.emit(f"{'jadd' if c > 0 else 'jsub'}<{j}>(J, {name});")
                 self.n_jterms += 1
         self.pending = {}
 
@@ -501,7 +500,7 @@ class Emitter:
         a = self.var("a")
         # with unit couplings in the currents the closure carries the top line's
         # kappa^(number of top-gluon vertices)
-        gk = f"c.gkp[{len(seq)}]" if self.vertex_kin else "c.gk"
+        gk = f"gkp_of(c, {len(seq)})" if self.vertex_kin else "c.gk"
         pair = self.lr_key(seq, j)
         if self.lr_uses.get(pair, 0) >= 2:
             # the pair closes several gluon trees in this group: its vector
@@ -512,13 +511,13 @@ class Emitter:
                 self.emit(f"const v4<T> {v} = vector_current({left}, {right});")
                 self.counts["vector_current"] += 1
                 self.vcur[pair] = v
-            self.emit(f"const cx<T> {a} = dot({cur}, {v}) * {gk};")
+            self.emit(f"const auto {a} = dot({cur}, {v}) * {gk};")
         elif "|".join(t.key for t in seq[j:]) in self.col_keys:
             # the column current through this vertex exists elsewhere in the
             # program: share its slashed product
-            self.emit(f"const cx<T> {a} = ffv_amp_col({left}, {cur}, {right}, {gk});")
+            self.emit(f"const auto {a} = ffv_amp_col({left}, {cur}, {right}, {gk});")
         else:
-            self.emit(f"const cx<T> {a} = ffv_amp({left}, {cur}, {right}, {gk});")
+            self.emit(f"const auto {a} = ffv_amp({left}, {cur}, {right}, {gk});")
         self.counts["ffv_amp"] += 1
         self.n_amp += 1
         self.accumulate(a, seq)
@@ -546,9 +545,9 @@ class Emitter:
         if t.kind == "v3":
             a = self.var("a")
             if unit:   # contracted term by term
-                self.emit(f"const cx<T> {a} = vvv_close({jtt}, {kids[0]}, {kids[1]}, {self.vmom(t)});")
+                self.emit(f"MGRW_CLOSE_V3({a}, {jtt}, {kids[0]}, {kids[1]}, ({self.vmom(t)}))")
             else:
-                self.emit(f"const cx<T> {a} = dot({jtt}, vvv({kids[0]}, {kids[1]}, {self.vmom(t)}, c.g));")
+                self.emit(f"const auto {a} = dot({jtt}, vvv({kids[0]}, {kids[1]}, {self.vmom(t)}, c.g));")
             self.counts["vvv_amp"] += 1
             self.n_amp += 1
             self.accumulate(a, seq)
@@ -559,16 +558,16 @@ class Emitter:
         if q is None:
             q = self.var("c")
             if unit:
-                self.emit(f"const auto {q} = vvvv_close({jtt}, {kids[0]}, {kids[1]}, {kids[2]});")
+                self.emit(f"MGRW_CLOSE_V4({q}, {jtt}, {kids[0]}, {kids[1]}, {kids[2]})")
             else:
                 self.emit(f"const auto {q} = vvvv({kids[0]}, {kids[1]}, {kids[2]}, c.g2);")
             self.counts["vvvv_amp"] += 1
             self.cache[rkey] = q
         a = self.var("a")
         if unit:
-            self.emit(f"const cx<T> {a} = {q}.{t.piece};")
+            self.emit(f"const auto {a} = {q}.{t.piece};")
         else:
-            self.emit(f"const cx<T> {a} = dot({jtt}, {q}.{t.piece});")
+            self.emit(f"const auto {a} = dot({jtt}, {q}.{t.piece});")
         self.n_amp += 1
         self.accumulate(a, seq)
 
@@ -798,20 +797,31 @@ def emit_process(name, ng, chunks=1, fp64_split=None, vertex_kin=False):
     w("  // momentum combinations of three-gluon vertices (V<S1>_<S2>) and the top-line")
     w("  // propagator momenta in light-cone form (QL, QR) for programs that read them,")
     w("  // and the inverse propagator denominators.")
+    # a record that is staged in LDS (one program per helicity) is laid out for
+    # the widest loads; the one-event-per-lane kernel's LDS slots stay as small as
+    # they can be, and records read through the scalar cache stay packed
+    staged = vertex_kin and chunks == 1
+    al = "alignas(16) " if staged else ""
     w("  template <typename T> struct kin {")
-    w("    T mt;")
+    if not staged:
+        w("    T mt;")
     if P_masks:
-        w("    r4<T> pt, ptb;")
+        w(f"    {al}r4<T> pt;")
+        w(f"    {al}r4<T> ptb;")
     for m in P_masks:
-        w(f"    r4<T> P{m};")
+        w(f"    {al}r4<T> P{m};")
     for m1, m2 in V_pairs:
-        w(f"    vvv_mom<T> V{m1}_{m2};")
-    for m in QL_masks:
-        w(f"    lc4<T> QL{m};")
-        w(f"    T mQL{m};")
-    for m in QR_masks:
-        w(f"    lc4<T> QR{m};")
-        w(f"    T mQR{m};")
+        w(f"    {al}vvv_mom<T> V{m1}_{m2};")
+    for side, masks in (("L", QL_masks), ("R", QR_masks)):
+        for m in masks:
+            w(f"    {al}lc4<T> Q{side}{m};")
+            if not staged:
+                w(f"    T mQ{side}{m};")
+    if staged:
+        w("    T mt;")
+        for side, masks in (("L", QL_masks), ("R", QR_masks)):
+            for m in masks:
+                w(f"    T mQ{side}{m};")
     for m in iP_masks:
         w(f"    T iP{m};")
     for m in qL_masks:
@@ -885,6 +895,30 @@ def emit_process(name, ng, chunks=1, fp64_split=None, vertex_kin=False):
     w(f"    w.ub = ubar_out<T>(b.t, (h >> {next_ - 1 - 2}) & 1 ? 1 : -1);")
     w(f"    w.v = v_out<T>(b.tb, (h >> {next_ - 1 - 3}) & 1 ? 1 : -1);")
     w("  }")
+    w("  // Both helicity states of every external particle: a wave's lanes, one")
+    w("  // configuration each, read theirs through ext_at (two addresses per particle).")
+    w("  template <typename T> struct ext_table {")
+    w("    pol4<T> e[NG][2];")
+    w("    sp<T> ub[2], v[2];")
+    w("  };")
+    w("  template <typename T>")
+    w("  static MGRW_HD void external_table(const basis<T>& b, ext_table<T>& t) {")
+    w("    for (int l = 0; l < 2; ++l) {")
+    for i, ip in enumerate(GLUON_PARTICLE[:ng]):
+        w(f"      t.e[{i}][l] = gluon_pol<T>(b.g{i}, 2 * l - 1, {'true' if ip >= 2 else 'false'});")
+    w("      t.ub[l] = ubar_out<T>(b.t, 2 * l - 1);")
+    w("      t.v[l] = v_out<T>(b.tb, 2 * l - 1);")
+    w("    }")
+    w("  }")
+    w("  template <typename T> struct ext_ref {")
+    w("    " + " ".join(f"const pol4<T>& e{i};" for i in range(ng)))
+    w("    const sp<T>& ub;")
+    w("    const sp<T>& v;")
+    w("  };")
+    w("  template <typename T> static MGRW_HD ext_ref<T> ext_at(const ext_table<T>& t, int h) {")
+    w("    return {" + ", ".join(f"t.e[{i}][(h >> {next_ - 1 - ip}) & 1]" for i, ip in enumerate(GLUON_PARTICLE[:ng])) +
+      f", t.ub[(h >> {next_ - 1 - 2}) & 1], t.v[(h >> {next_ - 1 - 3}) & 1]}};")
+    w("  }")
     if vertex_kin:
         # programs reading their vertex momenta from the record take unit strong
         # couplings (every diagram carries g^NG); kappa enters through gk and,
@@ -917,29 +951,35 @@ def emit_process(name, ng, chunks=1, fp64_split=None, vertex_kin=False):
     w("  // k: the event's kin<T> (in registers or in LDS).")
     if body is not None:
         w("  static constexpr int NCHUNK = 1;")
-        w("  template <typename T, typename KN>")
-        w("  static MGRW_HD void amplitude(const ext<T>& w, const KN& k, const coup<T>& c, cx<T>* J) {")
-        w("    for (int i = 0; i < K; ++i) J[i] = {T(0), T(0)};")
+        w("  // w: ext<T>, or an event's table through ext_at; c, J: the couplings and flows")
+        w("  // of one point, or of several (J zeroed by the caller).")
+        w("  template <typename T, typename W, typename KN, typename C, typename JA>")
+        w("  static MGRW_HD void program(const W& w, const KN& k, const C& c, JA&& J) {")
         for line in body:
             w("    " + line)
+        w("  }")
+        w("  template <typename T, typename W, typename KN>")
+        w("  static MGRW_HD void amplitude(const W& w, const KN& k, const coup<T>& c, cx<T>* J) {")
+        w("    for (int i = 0; i < K; ++i) J[i] = {T(0), T(0)};")
+        w("    program<T>(w, k, c, J);")
         w("  }")
     else:
         w(f"  static constexpr int NCHUNK = {len(part_ems)};")
         for ci, e in enumerate(part_ems):
             w(f"  // part {ci}: closing groups " + ", ".join(
                 "leaf" if g == "leaf" else str(bits(g)) for g in parts[ci]))
-            w("  template <typename T, typename KN>")
-            w(f"  static MGRW_HD void amplitude_part{ci}(const ext<T>& w, const KN& k, const coup<T>& c, cx<T>* J) {{")
+            w("  template <typename T, typename W, typename KN, typename C, typename JA>")
+            w(f"  static MGRW_HD void amplitude_part{ci}(const W& w, const KN& k, const C& c, JA&& J) {{")
             for line in e.lines:
                 w("    " + line)
             w("  }")
-        w("  template <int C, typename T, typename KN>")
-        w("  static MGRW_HD void amplitude_part(const ext<T>& w, const KN& k, const coup<T>& c, cx<T>* J) {")
+        w("  template <int C, typename T, typename W, typename KN, typename CP, typename JA>")
+        w("  static MGRW_HD void amplitude_part(const W& w, const KN& k, const CP& c, JA&& J) {")
         for ci in range(len(part_ems)):
             w(f"    {'if' if ci == 0 else 'else if'} constexpr (C == {ci}) amplitude_part{ci}<T>(w, k, c, J);")
         w("  }")
-        w("  template <typename T, typename KN>")
-        w("  static MGRW_HD void amplitude(const ext<T>& w, const KN& k, const coup<T>& c, cx<T>* J) {")
+        w("  template <typename T, typename W, typename KN>")
+        w("  static MGRW_HD void amplitude(const W& w, const KN& k, const coup<T>& c, cx<T>* J) {")
         w("    for (int i = 0; i < K; ++i) J[i] = {T(0), T(0)};")
         for ci in range(len(part_ems)):
             w(f"    amplitude_part{ci}<T>(w, k, c, J);")
@@ -955,13 +995,13 @@ def emit_process(name, ng, chunks=1, fp64_split=None, vertex_kin=False):
         for (c, r), (e, p) in sorted(fr_ems.items()):
             w(f"  // chunk {c} (closing groups " + ", ".join(
                 "leaf" if g == "leaf" else str(bits(g)) for g in p) + f"), flows {r * (K // nfr)}..{(r + 1) * (K // nfr) - 1}")
-            w("  template <typename T, typename KN>")
-            w(f"  static MGRW_HD void amplitude_fr{c}_{r}(const ext<T>& w, const KN& k, const coup<T>& c, cx<T>* J) {{")
+            w("  template <typename T, typename W, typename KN, typename C, typename JA>")
+            w(f"  static MGRW_HD void amplitude_fr{c}_{r}(const W& w, const KN& k, const C& c, JA&& J) {{")
             for line in e.lines:
                 w("    " + line)
             w("  }")
-        w("  template <int C, int R, typename T, typename KN>")
-        w("  static MGRW_HD void amplitude_fr(const ext<T>& w, const KN& k, const coup<T>& c, cx<T>* J) {")
+        w("  template <int C, int R, typename T, typename W, typename KN, typename CP, typename JA>")
+        w("  static MGRW_HD void amplitude_fr(const W& w, const KN& k, const CP& c, JA&& J) {")
         first = True
         for (c, r) in sorted(fr_ems):
             w(f"    {'if' if first else 'else if'} constexpr (C == {c} && R == {r}) amplitude_fr{c}_{r}<T>(w, k, c, J);")
@@ -973,8 +1013,8 @@ def emit_process(name, ng, chunks=1, fp64_split=None, vertex_kin=False):
         w("  // with k top-gluon vertices: J(g, kappa) = g^NG sum_k kappa^k J_k.")
         w("  // J: a pointer, or an accessor object with operator[] (entries kept partly")
         w("  // outside registers).")
-        w("  template <typename T, typename KN, typename JA>")
-        w("  static MGRW_HD void amplitude_kpoly(const ext<T>& w, const KN& k, const coup<T>& c, JA&& J) {")
+        w("  template <typename T, typename W, typename KN, typename JA>")
+        w("  static MGRW_HD void amplitude_kpoly(const W& w, const KN& k, const coup<T>& c, JA&& J) {")
         w("#if defined(__HIP_DEVICE_COMPILE__)")
         w("#pragma unroll")
         w("#endif")

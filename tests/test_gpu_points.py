@@ -1,0 +1,84 @@
+"""Several parameter points side by side in one pass of the one-event-per-wave
+kernels, and the split of a small batch's points over waves: each weight must be
+what its point gives alone, whatever its place in the pass, the number of
+points and the size of the batch.
+
+Single precision: bit for bit (a point's amplitude is rounded as in the program
+for one point).  Double precision: both results are held to 1e-12 of the
+oracle, so they agree to 2e-12."""
+import numpy as np
+import pytest
+
+from synth import generate_events, kappa_points
+
+pytestmark = pytest.mark.gpu
+FP64_TOL = 2e-12
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    return torch
+
+
+def handle(prec, npts, tau=None):
+    import paper_2312_07440_amd as mg
+    p = mg.Process("gg_ttgg", prec)
+    kap = kappa_points(npts)
+    p.set_params([{"kappa_ttg": float(k), "alphas": 0.118 * (1 + 0.01 * (i % 3))} for i, k in enumerate(kap)])
+    if tau is not None:
+        p.set_rescue_threshold(tau)
+    return p
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("npts", [1, 2, 3, 4, 5, 16, 64])
+@pytest.mark.parametrize("n", [1, 67])
+def test_every_point_as_alone(torch_dev, prec, npts, n):
+    torch = torch_dev
+    mom = torch.from_numpy(generate_events("gg_ttgg", n, first_event=3 * 10 ** 5)).cuda()
+    p = handle(prec, npts, 0.0 if prec == "mixed" else None)
+    w_in = torch.linspace(0.5, 2.0, n, dtype=torch.float64, device="cuda")
+    me0 = torch.empty(n, dtype=torch.float64, device="cuda")
+    out = p.reweight(mom, w_in=w_in, me_base_out=me0)
+    base = p.eval_me(mom)
+    ref = torch.stack([w_in * (p.eval_me(mom, point=k) / base) for k in range(npts)])
+    if prec == "mixed":
+        assert torch.equal(out, ref) and torch.equal(me0, base)
+    else:
+        assert (out / ref - 1).abs().max() <= FP64_TOL and (me0 / base - 1).abs().max() <= FP64_TOL
+
+
+@pytest.mark.parametrize("prec,tau", [("mixed", None), ("fp64", None), ("mixed", 1.0)])
+@pytest.mark.parametrize("n", [16383, 16384, 16387])
+def test_batch_size_does_not_matter(torch_dev, prec, tau, n):
+    """Both sides of the size from which on a wave takes a whole event (with
+    tau = 1 every event is re-evaluated in double precision, so the list of
+    those has the same sizes)."""
+    torch = torch_dev
+    mom = torch.from_numpy(generate_events("gg_ttgg", n, first_event=10 ** 6)).cuda()
+    p = handle(prec, 2, tau)
+    out = p.reweight(mom)
+    for sel in (slice(0, 131), slice(n - 70, n)):
+        part = p.reweight(mom[:, :, sel].contiguous())
+        assert torch.equal(out[:, sel], part)
+    if tau == 1.0:
+        ref = handle("fp64", 2).reweight(mom)
+        assert (out / ref - 1).abs().max() <= FP64_TOL
+
+
+@pytest.mark.parametrize("call", ["reweight", "reweight_noalloc"])
+def test_weights_in_place(torch_dev, call):
+    """The output may be the input weights' own buffer."""
+    torch = torch_dev
+    n = 300
+    mom = torch.from_numpy(generate_events("gg_ttgg", n, first_event=77)).cuda()
+    p = handle("mixed", 2)
+    w = torch.linspace(0.5, 2.0, n, dtype=torch.float64, device="cuda")
+    ref = p.reweight(mom, w_in=w)
+    for row in (0, 1):
+        buf = torch.zeros(2, n, dtype=torch.float64, device="cuda")
+        buf[row] = w
+        getattr(p, call)(mom, w_in=buf[row], out=buf)
+        assert torch.equal(buf, ref)
