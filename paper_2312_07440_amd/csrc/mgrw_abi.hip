@@ -295,6 +295,7 @@ mgrw_status mgrw_create_process(int proc, int prec, const mgrw_params* base, mgr
     p->colour_mfma = 0;
     p->hp = nullptr;
     p->sur_inputs = MGRW_SURROGATE_N_FEATURES;
+    pools().handle_created();
     *out = p;
     return MGRW_OK;
 }
@@ -438,6 +439,7 @@ void mgrw_destroy_process(mgrw_process* p) {
     mgrw::surrogate_destroy(p->sur);
     mgrw::host_pipeline_destroy(p->hp);
     delete p;
+    pools().handle_destroyed();
 }
 
 const char* mgrw_last_error(void) { return g_last_error.c_str(); }

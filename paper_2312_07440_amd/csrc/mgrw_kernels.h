@@ -10,6 +10,7 @@
 
 #include "../../include/mgrw.h"
 #include "mgrw_event.h"
+#include "mgrw_pool.h"
 
 namespace mgrw {
 
@@ -799,7 +800,7 @@ hipError_t launch_rescue(const double* mom, const double* w_in, int64_t n, const
             if (chunk < 1) return hipErrorInvalidValue;
             buf = static_cast<int64_t*>(a.scratch.ptr);
         } else {
-            hipError_t err = hipMallocAsync(reinterpret_cast<void**>(&buf), sizeof(int64_t) * size_t(n + 1), s);
+            hipError_t err = work_alloc(reinterpret_cast<void**>(&buf), sizeof(int64_t) * size_t(n + 1), s);
             if (err != hipSuccess) return err;
         }
         unsigned long long* count = reinterpret_cast<unsigned long long*>(buf);
@@ -865,7 +866,7 @@ hipError_t launch_wave_pipeline(const double* mom, const double* w_in, int64_t n
         if (chunk < 1) return hipErrorInvalidValue;
         if (chunk > n) chunk = n;
     } else {
-        hipError_t err = hipMallocAsync(reinterpret_cast<void**>(&mem), align256(sizeof(ED) * size_t(n)) + 512 +
+        hipError_t err = work_alloc(reinterpret_cast<void**>(&mem), align256(sizeof(ED) * size_t(n)) + 512 +
                                         words * align256(8 * size_t(n)), s);
         if (err != hipSuccess) return err;
     }
@@ -1346,9 +1347,9 @@ hipError_t launch_split64(const split_launchers<Proc>& L, const double* mom, int
     const int64_t B = part_batch<Proc, double>(slots, a.npts);
     ED* ev = nullptr;
     double* jbuf = nullptr;
-    hipError_t err = hipMallocAsync(reinterpret_cast<void**>(&ev), sizeof(ED) * size_t(slots), s);
+    hipError_t err = work_alloc(reinterpret_cast<void**>(&ev), sizeof(ED) * size_t(slots), s);
     if (err != hipSuccess) return err;
-    err = hipMallocAsync(reinterpret_cast<void**>(&jbuf),
+    err = work_alloc(reinterpret_cast<void**>(&jbuf),
                          sizeof(double) * size_t(B) * a.npts * 2 * Proc::K * Proc::NHEL, s);
     if (err != hipSuccess) {
         (void)hipFreeAsync(ev, s);
@@ -1429,12 +1430,12 @@ hipError_t launch_split(const split_launchers<Proc>& L, int fp64, const double* 
     ED* ev = nullptr;
     float* jbuf = nullptr;
     int64_t* buf = nullptr;
-    hipError_t err = hipMallocAsync(reinterpret_cast<void**>(&ev), sizeof(ED) * size_t(n), s);
+    hipError_t err = work_alloc(reinterpret_cast<void**>(&ev), sizeof(ED) * size_t(n), s);
     if (err != hipSuccess) return err;
-    err = hipMallocAsync(reinterpret_cast<void**>(&jbuf), sizeof(float) * size_t(B) * a.npts * 2 * Proc::K * Proc::NHEL,
+    err = work_alloc(reinterpret_cast<void**>(&jbuf), sizeof(float) * size_t(B) * a.npts * 2 * Proc::K * Proc::NHEL,
                          s);
     if (err == hipSuccess && rescue)
-        err = hipMallocAsync(reinterpret_cast<void**>(&buf), sizeof(int64_t) * size_t(n + 1), s);
+        err = work_alloc(reinterpret_cast<void**>(&buf), sizeof(int64_t) * size_t(n + 1), s);
     if (err != hipSuccess) {
         if (jbuf) (void)hipFreeAsync(jbuf, s);
         (void)hipFreeAsync(ev, s);

@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "mgrw_internal.h"
+#include "mgrw_pool.h"
 
 namespace mgrw {
 
@@ -991,7 +992,7 @@ struct sbuf {   // scratch of one call, allocated and freed in the order of its 
     sbuf(const sbuf&) = delete;
     sbuf& operator=(const sbuf&) = delete;
     hipError_t alloc(size_t count) {
-        return hipMallocAsync(reinterpret_cast<void**>(&p), std::max<size_t>(count, 1) * sizeof(T), s);
+        return work_alloc(reinterpret_cast<void**>(&p), std::max<size_t>(count, 1) * sizeof(T), s);
     }
     ~sbuf() {
         if (p) (void)hipFreeAsync(p, s);

@@ -11,6 +11,7 @@
 
 #include "../../include/mgrw.h"
 #include "mgrw_internal.h"
+#include "mgrw_pool.h"
 
 namespace {
 
@@ -99,7 +100,7 @@ extern "C" mgrw_status mgrw_multi_reweight(mgrw_process* const* procs, int n_pro
     };
     // per-process counts (the call synchronises once to size the batches)
     unsigned long long* counts = nullptr;
-    hipError_t err = hipMallocAsync(reinterpret_cast<void**>(&counts), sizeof(unsigned long long) * 2 * (kMaxProcs + 1), s);
+    hipError_t err = mgrw::work_alloc(reinterpret_cast<void**>(&counts), sizeof(unsigned long long) * 2 * (kMaxProcs + 1), s);
     if (err != hipSuccess) return dev_fail(err);
     unsigned long long* fill = counts + kMaxProcs + 1;
     hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s, counts, 2 * (kMaxProcs + 1));
@@ -128,7 +129,7 @@ extern "C" mgrw_status mgrw_multi_reweight(mgrw_process* const* procs, int n_pro
         // one allocation: momenta, weights, outputs, base |M|^2, origins
         const size_t doubles = size_t(np) * (size_t(ne) * 4 + 1 + size_t(n_points) + 1);
         double* buf = nullptr;
-        err = hipMallocAsync(reinterpret_cast<void**>(&buf), sizeof(double) * doubles + sizeof(int64_t) * size_t(np), s);
+        err = mgrw::work_alloc(reinterpret_cast<void**>(&buf), sizeof(double) * doubles + sizeof(int64_t) * size_t(np), s);
         if (err != hipSuccess) {
             result = dev_fail(err);
             break;

@@ -81,7 +81,7 @@ hipError_t launch(const double* mom, const double* w_in, int64_t n, const qed_la
         if (chunk < 1) return hipErrorInvalidValue;
         ev = static_cast<ee_5a::event<T>*>(a.scratch.ptr);
     } else {
-        hipError_t err = hipMallocAsync(reinterpret_cast<void**>(&ev), sizeof(ee_5a::event<T>) * size_t(n), s);
+        hipError_t err = work_alloc(reinterpret_cast<void**>(&ev), sizeof(ee_5a::event<T>) * size_t(n), s);
         if (err != hipSuccess) return err;
     }
     hipError_t err = hipSuccess;
