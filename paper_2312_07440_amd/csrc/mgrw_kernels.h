@@ -284,6 +284,35 @@ __device__ __forceinline__ const K& lds_near_use(const K& k) {
     return *p;
 }
 
+// The double-precision kernels' record and wavefunctions: every closing group
+// reads them through an address of its own.  Through one address for the
+// whole program the compiler keeps what several groups read, and the currents
+// formed from it, in registers from the first group to the last, and spills.
+template <class K>
+struct near_kin : K {};
+template <class K>
+__device__ __forceinline__ const near_kin<K>& near_view(const near_kin<K>& k) {
+    MGRW_SCHED_BARRIER();
+    return lds_near_use(k);
+}
+template <class E>
+struct near_ext : E {};
+struct near_lane {
+    template <class V>
+    __device__ __forceinline__ const V& operator()(const V& v) const {
+        const V* p = &v;
+        __asm__ volatile("" : "+v"(p));
+#if defined(__HIP_DEVICE_COMPILE__)
+        __builtin_assume(__builtin_amdgcn_is_shared(reinterpret_cast<const void*>(p)));
+#endif
+        return *p;
+    }
+};
+template <class E>
+__device__ __forceinline__ near_ext<E> near_view(const near_ext<E>& w) {
+    return {w.map(near_lane{})};
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -302,6 +331,8 @@ __device__ __forceinline__ double wave_sum(double v) {
 // wave per SIMD, two 7.9 ms, three 7.0 ms with 34 of the 72 accumulators in
 // LDS (7.8 with 26), four 8.9 ms.
 constexpr int kPointsF32 = 2, kPointsF64 = 3, kCellsF64 = 34;
+// The same for the split programs in double precision.
+constexpr int kPointsSplit64 = 2;
 template <typename T, int M>
 struct pass_plan {
     static constexpr int NL = sizeof(T) == 4 || M == 1 ? 0 : kCellsF64;
@@ -315,6 +346,21 @@ struct wave_slot {
     alignas(16) typename Proc::template ext_table<T> t;
     alignas(16) cx<T> j[64 * pass_plan<T, M>::NL + 1];
 };
+
+// Copy an event's record into the wave's slot.
+template <class D, class S>
+__device__ __forceinline__ void stage_record(const D& ev, S& s, int lane) {
+    static_assert(sizeof(s.k) % 4 == 0 && sizeof(s.t) % 4 == 0, "record copied in 32-bit words");
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(&ev.k);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(&s.k);
+    for (int i = lane; i < int(sizeof(s.k) / 4); i += 64) dst[i] = src[i];
+    src = reinterpret_cast<const uint32_t*>(&ev.t);
+    dst = reinterpret_cast<uint32_t*>(&s.t);
+    for (int i = lane; i < int(sizeof(s.t) / 4); i += 64) dst[i] = src[i];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // M points of an event evaluated side by side: the flows' accumulators.
 // In single precision the first point's are an array, as in a program for one
@@ -383,35 +429,76 @@ __device__ __forceinline__ void colour_points(point_acc<T, K, M>& J, double (&ac
 // them in the lane's LDS column (entry q at lds[64 q]) and the others in
 // registers.  The program's indices are constants, so each access resolves to
 // one storage at compile time.
+// Indices are expanded from packs, not loops: the entries in registers are then
+// values from the start, not an array that loops index until late in the
+// compilation (which left 2.2 times the spilled registers' worth of code).
 template <int K, int M, int NL>
 struct point_cells {
     cx<double>* lds;
     cx<double> reg[M * K - NL];
-    __device__ __forceinline__ cx<double>& at(int q) { return q < NL ? lds[64 * q] : reg[q - NL]; }
-    __device__ __forceinline__ void clear() {
-#pragma unroll
-        for (int q = 0; q < M * K; ++q) at(q) = {0.0, 0.0};
+    template <int Q>
+    __device__ __forceinline__ cx<double> get() const {
+        if constexpr (Q < NL)
+            return lds[64 * Q];
+        else
+            return reg[Q - NL];
+    }
+    template <int Q>
+    __device__ __forceinline__ void set(cx<double> x) {
+        if constexpr (Q < NL)
+            lds[64 * Q] = x;
+        else
+            reg[Q - NL] = x;
+    }
+    template <int... q>
+    __device__ __forceinline__ void clear(std::integer_sequence<int, q...>) { (set<q>({0.0, 0.0}), ...); }
+    __device__ __forceinline__ void clear() { clear(points_seq<M * K>{}); }
+    // point m's flows from / to memory (flow f at p[2 f stride], p[(2 f + 1) stride])
+    template <int m, int... f>
+    __device__ __forceinline__ void load(const double* p, int stride, std::integer_sequence<int, f...>) {
+        (set<m * K + f>({p[2 * f * stride], p[(2 * f + 1) * stride]}), ...);
+    }
+    template <int m, int... f>
+    __device__ __forceinline__ void store(double* p, int stride, std::integer_sequence<int, f...>) const {
+        ((p[2 * f * stride] = get<m * K + f>().re, p[(2 * f + 1) * stride] = get<m * K + f>().im), ...);
+    }
+    template <int m, int... f>
+    __device__ __forceinline__ void flows(cx<double>* J, std::integer_sequence<int, f...>) const {
+        ((J[f] = get<m * K + f>()), ...);
     }
 };
+template <int I, int K, int M, int NL, int... m>
+__device__ __forceinline__ void jadd_cells(point_cells<K, M, NL>& J, const cm<double, M>& s,
+                                           std::integer_sequence<int, m...>) {
+    (J.template set<m * K + I>(J.template get<m * K + I>() + s.v[m]), ...);
+}
+template <int I, int K, int M, int NL, int... m>
+__device__ __forceinline__ void jsub_cells(point_cells<K, M, NL>& J, const cm<double, M>& s,
+                                           std::integer_sequence<int, m...>) {
+    (J.template set<m * K + I>(J.template get<m * K + I>() - s.v[m]), ...);
+}
 template <int I, int K, int M, int NL>
 __device__ __forceinline__ void jadd(point_cells<K, M, NL>& J, const cm<double, M>& s) {
-#pragma unroll
-    for (int m = 0; m < M; ++m) J.at(m * K + I) = J.at(m * K + I) + s.v[m];
+    jadd_cells<I>(J, s, points_seq<M>{});
 }
 template <int I, int K, int M, int NL>
 __device__ __forceinline__ void jsub(point_cells<K, M, NL>& J, const cm<double, M>& s) {
-#pragma unroll
-    for (int m = 0; m < M; ++m) J.at(m * K + I) = J.at(m * K + I) - s.v[m];
+    jsub_cells<I>(J, s, points_seq<M>{});
+}
+template <class Proc, int m, int K, int M, int NL>
+__device__ __forceinline__ double colour_cell(const point_cells<K, M, NL>& J) {
+    cx<double> Jm[K];
+    J.template flows<m>(Jm, points_seq<K>{});
+    return Proc::colour_sum(Jm);
+}
+template <class Proc, int K, int M, int NL, int... m>
+__device__ __forceinline__ void colour_cells(const point_cells<K, M, NL>& J, double (&acc)[M],
+                                             std::integer_sequence<int, m...>) {
+    ((acc[m] += colour_cell<Proc, m>(J)), ...);
 }
 template <class Proc, int K, int M, int NL>
-__device__ __forceinline__ void colour_points(point_cells<K, M, NL>& J, double (&acc)[M]) {
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        cx<double> Jm[K];
-#pragma unroll
-        for (int i = 0; i < K; ++i) Jm[i] = J.at(m * K + i);
-        acc[m] += Proc::colour_sum(Jm);
-    }
+__device__ __forceinline__ void colour_points(const point_cells<K, M, NL>& J, double (&acc)[M]) {
+    colour_cells<Proc>(J, acc, points_seq<M>{});
 }
 
 template <class Proc, typename T, typename W, typename KN, typename C, typename JA>
@@ -512,18 +599,7 @@ qcd_wave_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t 
     using S = wave_slot<Proc, T, M>;
     __shared__ S sl[kBlock / 64];
     S& s = sl[wv];
-    {
-        static_assert(sizeof(s.k) % 4 == 0 && sizeof(s.t) % 4 == 0, "record copied in 32-bit words");
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(&ev[el].k);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(&s.k);
-        for (int i = lane; i < int(sizeof(s.k) / 4); i += 64) dst[i] = src[i];
-        src = reinterpret_cast<const uint32_t*>(&ev[el].t);
-        dst = reinterpret_cast<uint32_t*>(&s.t);
-        for (int i = lane; i < int(sizeof(s.t) / 4); i += 64) dst[i] = src[i];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
+    stage_record(ev[el], s, lane);
     const int k0 = int(id - el * units) * per * M, k1 = k0 + per * M < a.npts ? k0 + per * M : a.npts;
 #pragma unroll 1
     for (int kp = k0; kp < k1; kp += M) {
@@ -941,7 +1017,8 @@ hipError_t launch_kpoly(const double* mom, const double* w_in, int64_t n, const 
 // point and helicity of a batch of events, one event per wave with the
 // helicity configurations on the lanes.  The colour-flow amplitudes J travel
 // between the parts through HBM in a [event][point][component][helicity]
-// layout (consecutive lanes touch consecutive words).  By default the last
+// layout, the helicities in blocks of 64 (consecutive lanes touch consecutive
+// words, and one pass's flows are one contiguous piece).  By default the last
 // part forms the colour sum (VALU), the helicity sum (wave reduction) and the
 // reweighted weights; with the matrix-core colour sum selected it stores J
 // too, and qcd_colour_mfma_kernel contracts J with the colour matrix.
@@ -957,25 +1034,25 @@ struct mfma_colour<P, std::void_t<decltype(P::MFMA_COLOUR)>> : std::bool_constan
 #define MGRW_PART_WPE 1
 #endif
 
+// One wave's unit of work: points [u per, (u + 1) per) of one event.
 template <class Proc, typename T, int C, bool STORE_LAST>
 __global__ void __launch_bounds__(kBlock, MGRW_PART_WPE)
-qcd_part_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t nb, T* __restrict__ jbuf,
-                const double* __restrict__ w_in, int64_t n, qcd_launch a, double* __restrict__ out,
-                double* __restrict__ me0_out) {
+qcd_part_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t nb, T* __restrict__ jbuf, int64_t n,
+                int units, int per, qcd_launch a, double* __restrict__ out, double* __restrict__ me0) {
     constexpr int NH = Proc::NHEL, K2 = 2 * Proc::K;
     constexpr bool LAST = C + 1 == Proc::NCHUNK && !STORE_LAST;   // finishes the events here
     static_assert(NH % 64 == 0, "helicity configurations must fill whole waves");
-    const int64_t el = int64_t(blockIdx.x) * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t id = int64_t(blockIdx.x) * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t el = id / units;
     if (el >= nb) return;   // whole wave; no barriers below
     const int64_t e = e0 + el;
     if (ev[e].skip) return;   // left to the FP64 re-evaluation
     const int lane = threadIdx.x & 63;
     const typename Proc::template kin<T>& k = ev[e].k;
     const typename Proc::template basis<T>& b = ev[e].b;
-    const double w = (LAST && a.mode == 0 && w_in) ? w_in[e] : 1.0;
-    double me0 = 0.0;
+    const int k0 = int(id - el * units) * per, k1 = k0 + per < a.npts ? k0 + per : a.npts;
 #pragma unroll 1
-    for (int kp = 0; kp < a.npts; ++kp) {
+    for (int kp = k0; kp < k1; ++kp) {
         const qcd_point pt = a.pts[kp];
         const auto c = Proc::template couplings<T>(pt.gs, pt.gs2, pt.gk);
         double acc = 0.0;
@@ -983,23 +1060,23 @@ qcd_part_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t 
         for (int hc = 0; hc < NH; hc += 64) {
             __asm__ volatile("" ::: "memory");
             __shared__ lds_slot<typename Proc::template ext<T>> wfs[kBlock];
-            typename Proc::template ext<T>& wf = wfs[threadIdx.x].v;   // own slot, as in qcd_wave_kernel
+            typename Proc::template ext<T>& wf = wfs[threadIdx.x].v;   // own slot: in registers it would spill
             Proc::template external<T>(b, hc + lane, wf);
-            T* jp = jbuf + (el * a.npts + kp) * int64_t(K2) * NH + hc + lane;
+            T* jp = jbuf + (el * a.npts + kp) * int64_t(K2) * NH + hc * K2 + lane;
             cx<T> J[Proc::K];
             if constexpr (C == 0) {
 #pragma unroll
                 for (int f = 0; f < Proc::K; ++f) J[f] = {T(0), T(0)};
             } else {
 #pragma unroll
-                for (int f = 0; f < Proc::K; ++f) J[f] = {jp[(2 * f) * NH], jp[(2 * f + 1) * NH]};
+                for (int f = 0; f < Proc::K; ++f) J[f] = {jp[(2 * f) * 64], jp[(2 * f + 1) * 64]};
             }
             Proc::template amplitude_part<C, T>(wf, k, c, J);
             if constexpr (!LAST) {
 #pragma unroll
                 for (int f = 0; f < Proc::K; ++f) {
-                    jp[(2 * f) * NH] = J[f].re;
-                    jp[(2 * f + 1) * NH] = J[f].im;
+                    jp[(2 * f) * 64] = J[f].re;
+                    jp[(2 * f + 1) * 64] = J[f].im;
                 }
             } else {
                 acc += double(Proc::colour_sum(J));
@@ -1007,41 +1084,48 @@ qcd_part_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t 
         }
         if constexpr (LAST) {
             const double me = wave_sum(acc) * Proc::point_norm(pt.gs);
-            if (kp == 0) {
-                me0 = me;
-                if (lane == 0) {
-                    if (a.mode == 1)
-                        out[e] = me;
-                    else if (me0_out)
-                        me0_out[e] = me;
-                }
-            } else if (lane == 0) {
-                out[int64_t(kp - 1) * n + e] = reweighted(w, me, me0);
-            }
+            if (lane == 0) store_me(me, kp, e, e, n, a, out, me0);
         }
     }
 }
 
+// Waves that run at once at one per SIMD.
+constexpr int64_t kWaves1 = 1024;
+
+// Units per event of part C: whole events or single points.  A unit loads and
+// stores the flows once per pass either way, but a wave that goes on to its
+// event's next point overlaps its stores with that point's work: parts 1-3
+// take 13.9 / 16.2 / 21.3 ms for 6001 events x 17 points in whole events
+// against 23.0 / 18.5 / 23.1 in points, part 0, which loads no flows, 31.9
+// against 23.8.  Whole events, then, for parts that load flows, unless points
+// fill the chip so much better that they win in spite of that.
+template <int C>
+int split_units(int64_t nb, int npts) {
+    const int64_t whole = npts * ((nb + kWaves1 - 1) / kWaves1), points = (nb * npts + kWaves1 - 1) / kWaves1;
+    return C > 0 && 2 * whole <= 3 * points ? 1 : npts;
+}
+
 template <class Proc, typename T, int C>
-hipError_t launch_part(const event_data<Proc, T>* ev, int64_t e0, int64_t nb, T* jbuf, const double* w_in,
-                       int64_t n, const qcd_launch& a, double* out, double* me0, hipStream_t s) {
-    const dim3 grid(unsigned((nb + kBlock / 64 - 1) / (kBlock / 64)));
+hipError_t launch_part(const event_data<Proc, T>* ev, int64_t e0, int64_t nb, T* jbuf, int64_t n, const qcd_launch& a,
+                       double* out, double* me0, hipStream_t s) {
+    const int units = split_units<C>(nb, a.npts), per = a.npts / units;
+    const dim3 grid(unsigned((nb * units + kBlock / 64 - 1) / (kBlock / 64)));
     if constexpr (C + 1 == Proc::NCHUNK && mfma_colour<Proc>::value) {
         if (a.colour_mfma) {
-            hipLaunchKernelGGL((qcd_part_kernel<Proc, T, C, true>), grid, dim3(kBlock), 0, s, ev, e0, nb, jbuf, w_in, n,
-                               a, out, me0);
+            hipLaunchKernelGGL((qcd_part_kernel<Proc, T, C, true>), grid, dim3(kBlock), 0, s, ev, e0, nb, jbuf, n,
+                               units, per, a, out, me0);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((qcd_part_kernel<Proc, T, C, false>), grid, dim3(kBlock), 0, s, ev, e0, nb, jbuf, w_in, n, a,
-                       out, me0);
+    hipLaunchKernelGGL((qcd_part_kernel<Proc, T, C, false>), grid, dim3(kBlock), 0, s, ev, e0, nb, jbuf, n, units,
+                       per, a, out, me0);
     return hipGetLastError();
 }
 
 // ---------------------------------------------- colour sum on the matrix cores
 //
 // After the last program part, J of every (event, point, helicity) is in HBM
-// as X[c][n] (c = 2 flow + re/im, n = helicity).  Per event and point the
+// as X[c][n] (c = 2 flow + re/im, n = helicity; blocks of 64 helicities apart).  Per event and point the
 // colour sum over all helicities is
 //   sum_h J_h^+ CF J_h = sum_{f, n} X_f[n] (CF X)_f[n],
 // with X_f the 2 NHEL real columns (real and imaginary parts) of flow f.
@@ -1050,7 +1134,7 @@ hipError_t launch_part(const event_data<Proc, T>* ev, int64_t e0, int64_t nb, T*
 // X is split into three bfloat16 terms x1 + x2 + x3 (24 significant bits), and
 // the five products with weight above 2^-24 are accumulated in float32; the
 // final dot product uses X itself (float32) from HBM.  One workgroup (4 waves)
-// per event; each wave owns a quarter of D's columns.
+// per event and point; each wave owns a quarter of D's columns.
 
 typedef __attribute__((ext_vector_type(8))) __bf16 cbf16x8;
 typedef __attribute__((ext_vector_type(8))) unsigned short cu16x8;
@@ -1065,26 +1149,25 @@ __device__ __forceinline__ float bf16_float(unsigned short b) { return __uint_as
 
 template <class Proc>
 __global__ void __launch_bounds__(kBlock)
-qcd_colour_mfma_kernel(const float* __restrict__ jbuf, int64_t e0, int64_t nb, const double* __restrict__ w_in,
-                       int64_t n, qcd_launch a, double* __restrict__ out, double* __restrict__ me0_out) {
+qcd_colour_mfma_kernel(const float* __restrict__ jbuf, int64_t e0, int64_t nb, int64_t n, qcd_launch a,
+                       double* __restrict__ out, double* __restrict__ me0) {
     constexpr int K = Proc::K, KP = Proc::KP, NH = Proc::NHEL, NCOL = 2 * NH;
     static_assert(KP % 32 == 0 && NCOL % 128 == 0, "tile shapes");
     constexpr int MT = KP / 32, KS = KP / 16, NT_WAVE = NCOL / 32 / (kBlock / 64);
     const int64_t el = blockIdx.x;
     if (el >= nb) return;   // whole block
+    const int kp = blockIdx.y;
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int lr = lane & 31, lh = lane >> 5;
     __shared__ double part[kBlock / 64];
-    const double w = (a.mode == 0 && w_in) ? w_in[e0 + el] : 1.0;
-    double me0 = 0.0;
-#pragma unroll 1
-    for (int kp = 0; kp < a.npts; ++kp) {
+    {
         const float* X = jbuf + (el * a.npts + kp) * int64_t(2 * K) * NH;
         float s = 0.0f;
 #pragma unroll 1
         for (int t = 0; t < NT_WAVE; ++t) {
             const int ncol = (wv * NT_WAVE + t) * 32 + lr;   // this lane's column of D
             const int re_im = ncol / NH, h = ncol % NH;
+            const auto at = [&](int f) { return (h / 64 * 2 * K + 2 * f + re_im) * 64 + h % 64; };
             // B = X in three bfloat16 terms, all k-steps of this column tile
             cbf16x8 b1[KS], b2[KS], b3[KS];
 #pragma unroll
@@ -1093,7 +1176,7 @@ qcd_colour_mfma_kernel(const float* __restrict__ jbuf, int64_t e0, int64_t nb, c
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
                     const int f = ks * 16 + lh * 8 + r;
-                    const float x = f < K ? X[int64_t(2 * f + re_im) * NH + h] : 0.0f;
+                    const float x = f < K ? X[at(f)] : 0.0f;
                     const unsigned short x1 = bf16_rne(x);
                     const float r1 = x - bf16_float(x1);
                     const unsigned short x2 = bf16_rne(r1);
@@ -1129,7 +1212,7 @@ qcd_colour_mfma_kernel(const float* __restrict__ jbuf, int64_t e0, int64_t nb, c
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int f = mt * 32 + (r / 4) * 8 + lh * 4 + r % 4;
-                    if (f < K) s += X[int64_t(2 * f + re_im) * NH + h] * acc[r];
+                    if (f < K) s += X[at(f)] * acc[r];
                 }
             }
         }
@@ -1139,29 +1222,17 @@ qcd_colour_mfma_kernel(const float* __restrict__ jbuf, int64_t e0, int64_t nb, c
         double me = 0.0;
         for (int i = 0; i < kBlock / 64; ++i) me += part[i];
         me *= Proc::point_norm(a.pts[kp].gs);
-        __syncthreads();   // part[] is rewritten for the next point
-        if (threadIdx.x == 0) {
-            const int64_t e = e0 + el;
-            if (kp == 0) {
-                me0 = me;
-                if (a.mode == 1)
-                    out[e] = me;
-                else if (me0_out)
-                    me0_out[e] = me;
-            } else {
-                out[int64_t(kp - 1) * n + e] = reweighted(w, me, me0);
-            }
-        }
+        if (threadIdx.x == 0) store_me(me, kp, e0 + el, e0 + el, n, a, out, me0);
     }
 }
 
 template <class Proc>
-hipError_t launch_colour_mfma(const float* jbuf, int64_t e0, int64_t nb, const double* w_in, int64_t n,
-                              const qcd_launch& a, double* out, double* me0, hipStream_t s) {
+hipError_t launch_colour_mfma(const float* jbuf, int64_t e0, int64_t nb, int64_t n, const qcd_launch& a, double* out,
+                              double* me0, hipStream_t s) {
     if constexpr (mfma_colour<Proc>::value) {
         if (!a.colour_mfma) return hipSuccess;
-        hipLaunchKernelGGL((qcd_colour_mfma_kernel<Proc>), dim3(unsigned(nb)), dim3(kBlock), 0, s, jbuf, e0, nb, w_in,
-                           n, a, out, me0);
+        hipLaunchKernelGGL((qcd_colour_mfma_kernel<Proc>), dim3(unsigned(nb), unsigned(a.npts)), dim3(kBlock), 0, s,
+                           jbuf, e0, nb, n, a, out, me0);
         return hipGetLastError();
     } else {
         return hipSuccess;
@@ -1200,45 +1271,76 @@ qcd_setup64_kernel(const double* __restrict__ mom, int64_t n, double mt, const i
     ev[i].skip = 0;
 }
 
-template <class Proc, int C, int R>
+// M points a pass, as in qcd_wave_kernel, from the record staged in LDS; one
+// wave's unit of work is one pass of one slot.  Bound by FP64 issue at one wave
+// per SIMD and 512 registers; a diagram with terms in several ranges is
+// evaluated in each, so sharing the chains between points pays the more.
+// 700 events x 17 points: 42.6 ms with one point a pass, whole events per wave
+// and the record read through the scalar cache (874 scalar registers spilled
+// to vector lanes), 25.2 ms so.
+template <class Proc, int M>
+struct fr_plan {
+    // accumulators in LDS: what a quarter of the CU's 160 KiB leaves beside the record
+    static constexpr size_t record = sizeof(typename Proc::template kin<double>) +
+                                     sizeof(typename Proc::template ext_table<double>) + 64;
+    static constexpr int room = int((40 * 1024 - record) / 1024);
+    static constexpr int NL = M == 1 ? 0 : room;
+};
+template <class Proc, int M>
+struct fr_slot {
+    alignas(16) near_kin<typename Proc::template kin<double>> k;
+    alignas(16) typename Proc::template ext_table<double> t;
+    alignas(16) cx<double> j[64 * fr_plan<Proc, M>::NL + 1];
+};
+// The flows of M points, `point` values apart.
+template <int K, int M, int NL, int... m>
+__device__ __forceinline__ void load_points(point_cells<K, M, NL>& J, const double* p, int64_t point, int stride,
+                                            std::integer_sequence<int, m...>) {
+    (J.template load<m>(p + m * point, stride, points_seq<K>{}), ...);
+}
+template <int K, int M, int NL, int... m>
+__device__ __forceinline__ void store_points(const point_cells<K, M, NL>& J, double* p, int64_t point, int stride,
+                                             std::integer_sequence<int, m...>) {
+    (J.template store<m>(p + m * point, stride, points_seq<K>{}), ...);
+}
+// Points of the buffer per slot: whole passes, so that no load or store of a
+// pass depends on a point's existence (stores behind a condition put the
+// flows across a block boundary, and the register allocator spills ten times
+// as much).
+__host__ __device__ inline int split64_points(int npts) {
+    return npts > 1 ? (npts + kPointsSplit64 - 1) / kPointsSplit64 * kPointsSplit64 : 1;
+}
+template <class Proc, int C, int R, int M>
 __global__ void __launch_bounds__(kBlock, 1)
 qcd_fr_kernel(const event_data<Proc, double>* __restrict__ ev, const unsigned long long* __restrict__ count,
               int64_t e0, int64_t nb, double* __restrict__ jbuf, qcd_launch a) {
     constexpr int NH = Proc::NHEL, K2 = 2 * Proc::K, KR = Proc::KR;
     static_assert(NH % 64 == 0, "helicity configurations must fill whole waves");
-    const int64_t el = int64_t(blockIdx.x) * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t id = int64_t(blockIdx.x) * (kBlock / 64) + wv;
+    const int passes = (a.npts + M - 1) / M;
+    const int64_t el = id / passes;
     if (el >= nb) return;   // whole wave; no barriers below
     const int64_t i = e0 + el;
     if (count && i >= int64_t(count[0])) return;
     const int lane = threadIdx.x & 63;
-    const typename Proc::template kin<double>& k = ev[i].k;
-    const typename Proc::template basis<double>& b = ev[i].b;
+    __shared__ fr_slot<Proc, M> sl[kBlock / 64];
+    fr_slot<Proc, M>& s = sl[wv];
+    stage_record(ev[i], s, lane);
+    const int kp = int(id - el * passes) * M;
+    const auto c = couplings_of<Proc, double, M>(a.pts, kp, a.npts);
 #pragma unroll 1
-    for (int kp = 0; kp < a.npts; ++kp) {
-        const qcd_point pt = a.pts[kp];
-        const auto c = Proc::template couplings<double>(pt.gs, pt.gs2, pt.gk);
-#pragma unroll 1
-        for (int hc = 0; hc < NH; hc += 64) {
-            __asm__ volatile("" ::: "memory");
-            __shared__ lds_slot<typename Proc::template ext<double>> wfs[kBlock];
-            typename Proc::template ext<double>& wf = wfs[threadIdx.x].v;   // own slot
-            Proc::template external<double>(b, hc + lane, wf);
-            double* jp = jbuf + (el * a.npts + kp) * int64_t(K2) * NH + int64_t(2 * R * KR) * NH + hc + lane;
-            cx<double> J[KR];
-            if constexpr (C == 0) {
-#pragma unroll
-                for (int f = 0; f < KR; ++f) J[f] = {0.0, 0.0};
-            } else {
-#pragma unroll
-                for (int f = 0; f < KR; ++f) J[f] = {jp[(2 * f) * NH], jp[(2 * f + 1) * NH]};
-            }
-            Proc::template amplitude_fr<C, R, double>(wf, k, c, J);
-#pragma unroll
-            for (int f = 0; f < KR; ++f) {
-                jp[(2 * f) * NH] = J[f].re;
-                jp[(2 * f + 1) * NH] = J[f].im;
-            }
-        }
+    for (int hc = 0; hc < NH; hc += 64) {
+        __asm__ volatile("" ::: "memory");
+        const near_ext<typename Proc::template ext_ref<double>> w = {Proc::template ext_at<double>(s.t, hc + lane)};
+        point_cells<KR, M, fr_plan<Proc, M>::NL> J{&s.j[lane], {}};
+        double* jp = jbuf + (el * (passes * M) + kp) * int64_t(K2) * NH + hc * K2 + 2 * R * KR * 64 + lane;
+        if constexpr (C == 0)
+            J.clear();
+        else
+            load_points(J, jp, int64_t(K2) * NH, 64, points_seq<M>{});
+        Proc::template amplitude_fr<C, R, double>(w, s.k, c, J);
+        store_points(J, jp, int64_t(K2) * NH, 64, points_seq<M>{});
     }
 }
 
@@ -1252,71 +1354,62 @@ constexpr int kColourBlock = 40;
 template <class Proc>
 __global__ void __launch_bounds__(kBlock)
 qcd_colour64_kernel(const double* __restrict__ jbuf, const int64_t* __restrict__ list,
-                    const unsigned long long* __restrict__ count, int64_t e0, int64_t nb,
-                    const double* __restrict__ w_in, int64_t n, qcd_launch a, double* __restrict__ out,
-                    double* __restrict__ me0_out) {
+                    const unsigned long long* __restrict__ count, int64_t e0, int64_t nb, int64_t n, qcd_launch a,
+                    double* __restrict__ out, double* __restrict__ me0) {
     constexpr int K = Proc::K, NH = Proc::NHEL, BS = kColourBlock;
     static_assert(K % BS == 0, "colour blocks");
-    const int64_t el = int64_t(blockIdx.x) * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t unit = int64_t(blockIdx.x) * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t el = unit / a.npts;   // a unit: one point of one slot
     if (el >= nb) return;   // whole wave
     if (count && e0 + el >= int64_t(count[0])) return;
     const int64_t e = list ? list[e0 + el] : e0 + el;
     const int lane = threadIdx.x & 63;
-    const double w = (a.mode == 0 && w_in) ? w_in[e] : 1.0;
-    double me0 = 0.0;
+    const int kp = int(unit - el * a.npts);
+    double acc = 0.0;
 #pragma unroll 1
-    for (int kp = 0; kp < a.npts; ++kp) {
-        double acc = 0.0;
+    for (int hc = 0; hc < NH; hc += 64) {
+        const double* X = jbuf + (el * split64_points(a.npts) + kp) * int64_t(2 * K) * NH + hc * 2 * K + lane;
 #pragma unroll 1
-        for (int hc = 0; hc < NH; hc += 64) {
-            const double* X = jbuf + (el * a.npts + kp) * int64_t(2 * K) * NH + hc + lane;
-#pragma unroll 1
-            for (int a0 = 0; a0 < K; a0 += BS) {
-                double zr[BS], zi[BS];
+        for (int a0 = 0; a0 < K; a0 += BS) {
+            double zr[BS], zi[BS];
 #pragma unroll
-                for (int q = 0; q < BS; ++q) zr[q] = zi[q] = 0.0;
+            for (int q = 0; q < BS; ++q) zr[q] = zi[q] = 0.0;
 #pragma unroll 2
-                for (int t = 0; t < K; ++t) {
-                    const double jr = X[(2 * t) * NH], ji = X[(2 * t + 1) * NH];
-                    const double* cf = Proc::CF_DBL + t * K + a0;
+            for (int t = 0; t < K; ++t) {
+                const double jr = X[(2 * t) * 64], ji = X[(2 * t + 1) * 64];
+                const double* cf = Proc::CF_DBL + t * K + a0;
 #pragma unroll
-                    for (int q = 0; q < BS; ++q) {
-                        zr[q] = fma(cf[q], jr, zr[q]);
-                        zi[q] = fma(cf[q], ji, zi[q]);
-                    }
+                for (int q = 0; q < BS; ++q) {
+                    zr[q] = fma(cf[q], jr, zr[q]);
+                    zi[q] = fma(cf[q], ji, zi[q]);
                 }
+            }
 #pragma unroll
-                for (int q = 0; q < BS; ++q)
-                    acc += zr[q] * X[(2 * (a0 + q)) * NH] + zi[q] * X[(2 * (a0 + q) + 1) * NH];
-            }
-        }
-        const double me = wave_sum(acc) * Proc::point_norm(a.pts[kp].gs);
-        if (kp == 0) {
-            me0 = me;
-            if (lane == 0) {
-                if (a.mode == 1)
-                    out[e] = me;
-                else if (me0_out)
-                    me0_out[e] = me;
-            }
-        } else if (lane == 0) {
-            out[int64_t(kp - 1) * n + e] = reweighted(w, me, me0);
+            for (int q = 0; q < BS; ++q)
+                acc += zr[q] * X[(2 * (a0 + q)) * 64] + zi[q] * X[(2 * (a0 + q) + 1) * 64];
         }
     }
+    const double me = wave_sum(acc) * Proc::point_norm(a.pts[kp].gs);
+    if (lane == 0) store_me(me, kp, e, e, n, a, out, me0);
 }
 
 template <class Proc, int C, int R>
 hipError_t launch_fr(const event_data<Proc, double>* ev, const unsigned long long* count, int64_t e0, int64_t nb,
                      double* jbuf, const qcd_launch& a, hipStream_t s) {
-    const dim3 grid(unsigned((nb + kBlock / 64 - 1) / (kBlock / 64)));
-    hipLaunchKernelGGL((qcd_fr_kernel<Proc, C, R>), grid, dim3(kBlock), 0, s, ev, count, e0, nb, jbuf, a);
+    const int64_t passes = a.npts > 1 ? (a.npts + kPointsSplit64 - 1) / kPointsSplit64 : 1;
+    const dim3 grid(unsigned((nb * passes + kBlock / 64 - 1) / (kBlock / 64)));
+    if (a.npts > 1)
+        hipLaunchKernelGGL((qcd_fr_kernel<Proc, C, R, kPointsSplit64>), grid, dim3(kBlock), 0, s, ev, count, e0, nb,
+                           jbuf, a);
+    else
+        hipLaunchKernelGGL((qcd_fr_kernel<Proc, C, R, 1>), grid, dim3(kBlock), 0, s, ev, count, e0, nb, jbuf, a);
     return hipGetLastError();
 }
 
 // Kernel launchers of a split program, one translation unit each.
 template <class Proc>
 struct split_launchers {
-    using part_fn = hipError_t (*)(const event_data<Proc, float>*, int64_t, int64_t, float*, const double*, int64_t,
+    using part_fn = hipError_t (*)(const event_data<Proc, float>*, int64_t, int64_t, float*, int64_t,
                                    const qcd_launch&, double*, double*, hipStream_t);
     using fr_fn = hipError_t (*)(const event_data<Proc, double>*, const unsigned long long*, int64_t, int64_t,
                                  double*, const qcd_launch&, hipStream_t);
@@ -1325,14 +1418,17 @@ struct split_launchers {
 };
 
 // Events per batch of the split programs: the buffer that carries J between
-// the parts holds batch x points x 2K x NHEL values of T, about 16 GiB at most.
+// the parts holds batch x points x 2K x NHEL values of T, about 4.5 GiB at
+// most, and a batch of more than one round of waves is a whole number of them
+// (17 points: 2048 events in single and 1024 in double precision).
 constexpr int64_t kPartBatch = 8192;
-constexpr size_t kJBufBytes = size_t(16) << 30;
+constexpr size_t kJBufBytes = size_t(9) << 29;
 template <class Proc, typename T>
 int64_t part_batch(int64_t n, int npts) {
     const size_t per_event = size_t(npts) * 2 * Proc::K * Proc::NHEL * sizeof(T);
     int64_t b = int64_t(kJBufBytes / per_event);
     b = b > kPartBatch ? kPartBatch : (b < 64 ? 64 : b);
+    if (b > kWaves1) b -= b % kWaves1;
     return n < b ? n : b;
 }
 
@@ -1341,16 +1437,17 @@ int64_t part_batch(int64_t n, int npts) {
 // i is event i; otherwise slot i is event list[i] for i < count[0].
 template <class Proc>
 hipError_t launch_split64(const split_launchers<Proc>& L, const double* mom, int64_t n, const int64_t* list,
-                          const unsigned long long* count, int64_t slots, const double* w_in, const qcd_launch& a,
-                          double* out, double* me0, hipStream_t s, bool timed) {
+                          const unsigned long long* count, int64_t slots, const qcd_launch& a, double* out,
+                          double* me0, hipStream_t s, bool timed) {
     using ED = event_data<Proc, double>;
-    const int64_t B = part_batch<Proc, double>(slots, a.npts);
+    const int jpts = split64_points(a.npts);
+    const int64_t B = part_batch<Proc, double>(slots, jpts);
     ED* ev = nullptr;
     double* jbuf = nullptr;
     hipError_t err = work_alloc(reinterpret_cast<void**>(&ev), sizeof(ED) * size_t(slots), s);
     if (err != hipSuccess) return err;
     err = work_alloc(reinterpret_cast<void**>(&jbuf),
-                         sizeof(double) * size_t(B) * a.npts * 2 * Proc::K * Proc::NHEL, s);
+                         sizeof(double) * size_t(B) * jpts * 2 * Proc::K * Proc::NHEL, s);
     if (err != hipSuccess) {
         (void)hipFreeAsync(ev, s);
         return err;
@@ -1400,8 +1497,9 @@ hipError_t launch_split64(const split_launchers<Proc>& L, const double* mom, int
             }
         }
         if (err == hipSuccess) {
-            hipLaunchKernelGGL((qcd_colour64_kernel<Proc>), dim3(unsigned((nb + kBlock / 64 - 1) / (kBlock / 64))),
-                               dim3(kBlock), 0, s, jbuf, list, count, e0, nb, w_in, n, a, out, me0);
+            hipLaunchKernelGGL((qcd_colour64_kernel<Proc>),
+                               dim3(unsigned((nb * a.npts + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0, s,
+                               jbuf, list, count, e0, nb, n, a, out, me0);
             err = hipGetLastError();
         }
     }
@@ -1414,16 +1512,16 @@ hipError_t launch_split64(const split_launchers<Proc>& L, const double* mom, int
     return err != hipSuccess ? err : (f1 != hipSuccess ? f1 : f2);
 }
 
-// A split program: FP64 runs the double-precision pipeline over all events;
-// mixed precision runs the per-event data (listing ill-conditioned events
-// when the re-evaluation is on), batches through the single-precision parts
-// (and the matrix-core colour sum when selected), then the listed events
-// through the double-precision pipeline.
+// |M|^2 of a split program to out and me0 (per event).  FP64 runs the
+// double-precision pipeline over all events; mixed precision runs the
+// per-event data (listing ill-conditioned events when the re-evaluation is
+// on), batches through the single-precision parts (and the matrix-core colour
+// sum when selected), then the listed events through the double-precision
+// pipeline.
 template <class Proc>
-hipError_t launch_split(const split_launchers<Proc>& L, int fp64, const double* mom, const double* w_in, int64_t n,
-                        const qcd_launch& a, double* out, double* me0, hipStream_t s) {
-    if (a.scratch.ptr) return hipErrorNotSupported;   // J buffers of MBs per event: always allocated
-    if (fp64) return launch_split64<Proc>(L, mom, n, nullptr, nullptr, n, w_in, a, out, me0, s, true);
+hipError_t launch_split_me(const split_launchers<Proc>& L, int fp64, const double* mom, int64_t n, const qcd_launch& a,
+                           double* out, double* me0, hipStream_t s) {
+    if (fp64) return launch_split64<Proc>(L, mom, n, nullptr, nullptr, n, a, out, me0, s, true);
     using ED = event_data<Proc, float>;
     const bool rescue = a.rescue_tau > 0.0;
     const int64_t B = part_batch<Proc, float>(n, a.npts);
@@ -1451,15 +1549,44 @@ hipError_t launch_split(const split_launchers<Proc>& L, int fp64, const double* 
     for (int64_t e0 = 0; e0 < n && err == hipSuccess; e0 += B) {
         const int64_t nb = n - e0 < B ? n - e0 : B;
         for (int c = 0; c < Proc::NCHUNK && err == hipSuccess; ++c)
-            err = L.part[c](ev, e0, nb, jbuf, w_in, n, a, out, me0, s);
-        if (err == hipSuccess) err = launch_colour_mfma<Proc>(jbuf, e0, nb, w_in, n, a, out, me0, s);
+            err = L.part[c](ev, e0, nb, jbuf, n, a, out, me0, s);
+        if (err == hipSuccess) err = launch_colour_mfma<Proc>(jbuf, e0, nb, n, a, out, me0, s);
     }
     mark(a.t1, s);
     hipError_t f1 = hipFreeAsync(jbuf, s), f2 = hipFreeAsync(ev, s);
-    if (err == hipSuccess && rescue)
-        err = launch_split64<Proc>(L, mom, n, list, count, n, w_in, a, out, me0, s, false);
+    if (err == hipSuccess && rescue) err = launch_split64<Proc>(L, mom, n, list, count, n, a, out, me0, s, false);
     hipError_t f3 = rescue ? hipFreeAsync(buf, s) : hipSuccess;
     return err != hipSuccess ? err : (f1 != hipSuccess ? f1 : (f2 != hipSuccess ? f2 : f3));
+}
+
+// A split program: |M|^2 of every event and point, then the weights.
+template <class Proc>
+hipError_t launch_split(const split_launchers<Proc>& L, int fp64, const double* mom, const double* w_in, int64_t n,
+                        const qcd_launch& a, double* out, double* me0, hipStream_t s) {
+    if (a.scratch.ptr) return hipErrorNotSupported;   // J buffers of MBs per event: always allocated
+    const bool weights = a.mode == 0;
+    const bool base = weights && !me0;
+    const bool aside = weights && (overlap(w_in, n, out, (a.npts - 1) * n) || overlap(w_in, n, me0, n));
+    double* buf = nullptr;
+    if (base || aside) {
+        hipError_t err = work_alloc(reinterpret_cast<void**>(&buf), 16 * size_t(n), s);
+        if (err != hipSuccess) return err;
+    }
+    const unsigned blocks = unsigned((n + kBlock - 1) / kBlock);
+    const double* w = w_in;
+    if (aside) {
+        hipLaunchKernelGGL((copy_weights_kernel<kBlock>), dim3(blocks), dim3(kBlock), 0, s, w_in, n, buf + n);
+        w = buf + n;
+    }
+    double* m0 = base ? buf : me0;
+    hipError_t err = launch_split_me<Proc>(L, fp64, mom, n, a, out, m0, s);
+    if (err == hipSuccess && weights && a.npts > 1) {
+        hipLaunchKernelGGL((reweight_ratio_kernel<kBlock>), dim3(blocks, unsigned(a.npts - 1)), dim3(kBlock), 0, s, w,
+                           m0, int64_t(0), n, n, out);
+        err = hipGetLastError();
+    }
+    const hipError_t ferr = buf ? hipFreeAsync(buf, s) : hipSuccess;
+    return err != hipSuccess ? err : ferr;
 }
 
 // Launch the reweight (mode 0) or single-point (mode 1) kernels of Proc at the

@@ -38,6 +38,10 @@
 
 namespace mgrw {
 
+// The record or the wavefunctions as one closing group of a program reads
+// them: themselves, unless the kernel's type for them has a view per group.
+template <typename V> MGRW_HD const V& near_view(const V& v) { return v; }
+
 struct zero {};
 
 template <typename T>

@@ -53,13 +53,13 @@ def generate(outdir=None, procs=None, force=False):
                     f"    return launch_qcd<{name}>(fp64, mom, w_in, n, a, out, me0, s);\n}}\n")
         else:
             psig = (f"(const event_data<{name}, float>* ev, int64_t e0, int64_t nb, float* jbuf,\n"
-                    "    const double* w_in, int64_t n, const qcd_launch& a, double* out, double* me0, hipStream_t s)")
+                    "    int64_t n, const qcd_launch& a, double* out, double* me0, hipStream_t s)")
             fsig = (f"(const event_data<{name}, double>* ev, const unsigned long long* count, int64_t e0,\n"
                     "    int64_t nb, double* jbuf, const qcd_launch& a, hipStream_t s)")
             for c in range(nch):
                 put(os.path.join(outdir, f"qcd_{name}_part{c}.hip"),
                     head + f"hipError_t launch_{name}_part{c}{psig} {{\n"
-                    f"    return launch_part<{name}, float, {c}>(ev, e0, nb, jbuf, w_in, n, a, out, me0, s);\n}}\n"
+                    f"    return launch_part<{name}, float, {c}>(ev, e0, nb, jbuf, n, a, out, me0, s);\n}}\n"
                     "}  // namespace mgrw\n")
             nch64, nfr = FP64_SPLIT[name]
             frs = [(c, r) for c in range(nch64) for r in range(nfr)]

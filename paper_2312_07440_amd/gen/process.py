@@ -46,6 +46,8 @@ from functools import lru_cache
 from itertools import permutations
 
 GLUON_PARTICLE = (0, 1, 4, 5, 6)
+# statements of a program per view of the record (see Emitter.open_view)
+VIEW_EVERY = 40
 
 
 def bits(mask):
@@ -333,6 +335,10 @@ class Emitter:
         self.global_cache = {}
         self.cache = {}
         self.global_leaf_lr = global_leaf_lr
+        # names of the record and the wavefunctions in the current stretch of the
+        # program (near_view: a kernel may give each stretch a view of its own)
+        self.k, self.w = "k", "w"
+        self.n_views = self.since_view = 0
 
     def var(self, prefix):
         self.nvar += 1
@@ -340,6 +346,15 @@ class Emitter:
 
     def emit(self, line):
         self.lines.append(line)
+        self.since_view += 1
+        if self.since_view >= VIEW_EVERY:
+            self.open_view()
+
+    def open_view(self):
+        self.n_views += 1
+        self.k, self.w = f"k{self.n_views}", f"w{self.n_views}"
+        self.lines.append(f"const auto& {self.k} = near_view(k); const auto& {self.w} = near_view(w);")
+        self.since_view = 0
 
     def lookup(self, key):
         if key in self.cache:
@@ -351,20 +366,18 @@ class Emitter:
         m1, m2 = t.kids[0].mask, t.kids[1].mask
         if self.vertex_kin:
             self.V_needed.add((m1, m2))
-            return f"k.V{m1}_{m2}"
+            return f"{self.k}.V{m1}_{m2}"
         self.P_needed |= {m1, m2}
-        return f"vvv_mom_of(k.P{m1}, k.P{m2})"
+        return f"vvv_mom_of({self.k}.P{m1}, {self.k}.P{m2})"
 
     # ---- gluon trees
     def tree(self, t):
+        if t.kind == "leaf":
+            return f"{self.w}.e{bits(t.mask)[0]}"
         key = "T:" + t.key
         v = self.lookup(key)
         if v:
             return v
-        if t.kind == "leaf":
-            name = f"w.e{bits(t.mask)[0]}"
-            self.global_cache[key] = name
-            return name
         kids = [self.tree(k) for k in t.kids]
         self.iP_needed.add(t.mask)
         if t.kind == "v3":
@@ -372,13 +385,13 @@ class Emitter:
             if self.vertex_kin:   # the record's vertex momenta carry 1/P^2; unit coupling
                 self.emit(f"const v4<T> {name} = vvv({kids[0]}, {kids[1]}, {self.vmom(t)});")
             else:
-                self.emit(f"const v4<T> {name} = vvv({kids[0]}, {kids[1]}, {self.vmom(t)}, c.g * k.iP{t.mask});")
+                self.emit(f"const v4<T> {name} = vvv({kids[0]}, {kids[1]}, {self.vmom(t)}, c.g * {self.k}.iP{t.mask});")
             self.counts["vvv"] += 1
             self.cache[key] = name
             return name
         q = self.var("c")
         g2 = "" if self.vertex_kin else "c.g2 * "
-        self.emit(f"const auto {q} = vvvv({kids[0]}, {kids[1]}, {kids[2]}, {g2}k.iP{t.mask});")
+        self.emit(f"const auto {q} = vvvv({kids[0]}, {kids[1]}, {kids[2]}, {g2}{self.k}.iP{t.mask});")
         self.counts["vvvv"] += 1
         inner = ",".join(k.key for k in t.kids)
         for p in "ABC":
@@ -389,7 +402,7 @@ class Emitter:
     def L(self, seq):
         """Row current ubar Gamma(T1) S Gamma(T2) S ... Gamma(Tj) S."""
         if not seq:
-            return "w.ub"
+            return f"{self.w}.ub"
         key = "L:" + "|".join(t.key for t in seq)
         v = self.lookup(key)
         if v:
@@ -403,10 +416,10 @@ class Emitter:
         name = self.var("l")
         if self.vertex_kin:   # momentum and mass carry 1/(q^2 - m^2); unit coupling
             self.QL_needed.add(mask)
-            self.emit(f"const sp<T> {name} = ffv_row({prev}, {cur}, k.QL{mask}, k.mQL{mask});")
+            self.emit(f"const sp<T> {name} = ffv_row({prev}, {cur}, {self.k}.QL{mask}, {self.k}.mQL{mask});")
         else:
             self.P_needed.add(mask)
-            self.emit(f"const sp<T> {name} = ffv_row({prev}, {cur}, k.pt - k.P{mask}, k.mt, c.gk * k.iqL{mask});")
+            self.emit(f"const sp<T> {name} = ffv_row({prev}, {cur}, {self.k}.pt - {self.k}.P{mask}, {self.k}.mt, c.gk * {self.k}.iqL{mask});")
         self.counts["ffv_row"] += 1
         glob = self.global_leaf_lr and len(seq) == 1 and seq[0].kind == "leaf"
         (self.global_cache if glob else self.cache)[key] = name
@@ -415,7 +428,7 @@ class Emitter:
     def R(self, seq):
         """Column current S Gamma(T1) S Gamma(T2) ... Gamma(Tk) v."""
         if not seq:
-            return "w.v"
+            return f"{self.w}.v"
         key = "R:" + "|".join(t.key for t in seq)
         v = self.lookup(key)
         if v:
@@ -429,10 +442,10 @@ class Emitter:
         name = self.var("r")
         if self.vertex_kin:
             self.QR_needed.add(mask)
-            self.emit(f"const sp<T> {name} = ffv_col({cur}, {nxt}, k.QR{mask}, k.mQR{mask});")
+            self.emit(f"const sp<T> {name} = ffv_col({cur}, {nxt}, {self.k}.QR{mask}, {self.k}.mQR{mask});")
         else:
             self.P_needed.add(mask)
-            self.emit(f"const sp<T> {name} = ffv_col({cur}, {nxt}, k.P{mask} - k.ptb, k.mt, c.gk * k.iqR{mask});")
+            self.emit(f"const sp<T> {name} = ffv_col({cur}, {nxt}, {self.k}.P{mask} - {self.k}.ptb, {self.k}.mt, c.gk * {self.k}.iqR{mask});")
         self.counts["ffv_col"] += 1
         glob = self.global_leaf_lr and len(seq) == 1 and seq[0].kind == "leaf"
         (self.global_cache if glob else self.cache)[key] = name
@@ -443,7 +456,7 @@ class Emitter:
         if v:
             return v
         self.iP_needed.add(self.full)
-        self.emit(f"const auto jtt = tt_current(w.ub, w.v, gk_of(c), k.iP{self.full});")
+        self.emit(f"const auto jtt = tt_current({self.w}.ub, {self.w}.v, gk_of(c), {self.k}.iP{self.full});")
         self.counts["tt_current"] += 1
         self.global_cache["Jtt"] = "jtt"
         return "jtt"
@@ -612,6 +625,7 @@ class Emitter:
         leaf.sort(key=lambda x: ([t.key for t in x[0][x[1] + 1:]], [t.key for t in x[0]]))
         if only is None or "leaf" in only:
             self.emit("// leaf-only diagrams")
+            self.open_view()
             self.count_pairs(leaf)
             for seq, j in leaf:
                 self.close_ttg(seq, j)
@@ -634,6 +648,7 @@ class Emitter:
             items.sort(key=lambda it: (anchor(it), it[0], [t.key for t in it[1]]))
             self.emit("MGRW_SCHED_BARRIER();")
             self.emit(f"// closing trees over gluons {bits(U)}")
+            self.open_view()
             self.count_pairs([(seq, j) for kind, seq, j in items if kind == "ttg"])
             for kind, seq, j in items:
                 if kind == "ttg":
@@ -914,6 +929,9 @@ def emit_process(name, ng, chunks=1, fp64_split=None, vertex_kin=False):
     w("    " + " ".join(f"const pol4<T>& e{i};" for i in range(ng)))
     w("    const sp<T>& ub;")
     w("    const sp<T>& v;")
+    w("    template <typename F> MGRW_HD ext_ref map(F f) const {")
+    w("      return {" + ", ".join(f"f(e{i})" for i in range(ng)) + ", f(ub), f(v)};")
+    w("    }")
     w("  };")
     w("  template <typename T> static MGRW_HD ext_ref<T> ext_at(const ext_table<T>& t, int h) {")
     w("    return {" + ", ".join(f"t.e[{i}][(h >> {next_ - 1 - ip}) & 1]" for i, ip in enumerate(GLUON_PARTICLE[:ng])) +

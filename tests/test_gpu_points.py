@@ -82,3 +82,63 @@ def test_weights_in_place(torch_dev, call):
         buf[row] = w
         getattr(p, call)(mom, w_in=buf[row], out=buf)
         assert torch.equal(buf, ref)
+
+
+def split_handle(prec, npts, tau=None):
+    import paper_2312_07440_amd as mg
+    p = mg.Process("gg_ttggg", prec)
+    p.set_params([{"kappa_ttg": float(k), "alphas": 0.118 * (1 + 0.01 * (i % 3))}
+                  for i, k in enumerate(kappa_points(npts))])
+    if tau is not None:
+        p.set_rescue_threshold(tau)
+    return p
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("npts", [1, 2, 3, 16])
+def test_split_program_every_point_as_alone(torch_dev, prec, npts):
+    torch = torch_dev
+    n = 5
+    mom = torch.from_numpy(generate_events("gg_ttggg", n, first_event=3 * 10 ** 5)).cuda()
+    p = split_handle(prec, npts, 0.0 if prec == "mixed" else None)
+    w_in = torch.linspace(0.5, 2.0, n, dtype=torch.float64, device="cuda")
+    me0 = torch.empty(n, dtype=torch.float64, device="cuda")
+    out = p.reweight(mom, w_in=w_in, me_base_out=me0)
+    base = p.eval_me(mom)
+    ref = torch.stack([w_in * (p.eval_me(mom, point=k) / base) for k in range(npts)])
+    if prec == "mixed":
+        assert torch.equal(out, ref) and torch.equal(me0, base)
+    else:
+        assert (out / ref - 1).abs().max() <= FP64_TOL and (me0 / base - 1).abs().max() <= FP64_TOL
+
+
+@pytest.mark.parametrize("prec,npts,n", [("mixed", 3, 340), ("mixed", 3, 1025), ("mixed", 16, 2100), ("fp64", 2, 70),
+                                         ("fp64", 16, 1030)])
+def test_split_program_batch_size_does_not_matter(torch_dev, prec, npts, n):
+    """Single points and whole events per wave, one batch and several."""
+    torch = torch_dev
+    mom = torch.from_numpy(generate_events("gg_ttggg", n, first_event=10 ** 6)).cuda()
+    p = split_handle(prec, npts)
+    out = p.reweight(mom)
+    for sel in (slice(0, 9), slice(n - 11, n)):
+        assert torch.equal(out[:, sel], p.reweight(mom[:, :, sel].contiguous()))
+
+
+def test_buffers_survive_handles_and_streams(torch_dev):
+    """The library's memory pool: calls on two streams, handles created and
+    destroyed between them, the same weights every time."""
+    torch = torch_dev
+    mom = torch.from_numpy(generate_events("gg_ttgg", 2000, first_event=5)).cuda()
+    ref = handle("mixed", 4).reweight(mom)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    outs = []
+    for i in range(6):
+        p = handle("mixed", 4)
+        with torch.cuda.stream(streams[i % 2]):
+            outs.append(p.reweight(mom))
+        if i % 3 == 2:
+            torch.cuda.synchronize()
+        p.close()
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, ref) for o in outs)
