@@ -8,9 +8,9 @@
 // the base point and at every new parameter point and writes the reweighted
 // weights (Sec. 3.2, steps 3-8; eq. (3)).  QCD processes whose number of
 // helicity configurations is a multiple of 64 run one event per 64-lane wave
-// with the configurations on the lanes (mgrw_kernels.h); the others one event
-// per lane with a wave-uniform helicity loop, so lanes never diverge inside
-// the diagram chains.
+// with the configurations on the lanes (mgrw_kernels.h); the others several
+// events per wave, or one per lane with a wave-uniform helicity loop; lanes
+// never diverge inside the diagram chains.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -185,9 +185,9 @@ mgrw_status run(mgrw_process* p, const double* mom, const double* w_in, int64_t 
     a.mode = mode;
     a.mt = p->base.mt;
     // automatic choice: one event per wave when the helicity configurations fill
-    // whole waves (kinematics then live in the scalar cache, not in VGPRs/LDS)
+    // whole waves; the others choose by the batch (launch_main)
     a.mapping = p->mapping != MGRW_MAP_AUTO ? p->mapping
-                : (info_of(p->proc).n_hel % 64 == 0 ? MGRW_MAP_EVENT_PER_WAVE : MGRW_MAP_EVENT_PER_LANE);
+                : (info_of(p->proc).n_hel % 64 == 0 ? MGRW_MAP_EVENT_PER_WAVE : MGRW_MAP_AUTO);
     a.kpoly = kpoly;
     a.rescue_tau = p->rescue_tau;
     a.colour_mfma = p->colour_mfma;

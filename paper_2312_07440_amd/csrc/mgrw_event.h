@@ -82,6 +82,28 @@ MGRW_HD double point_me(const KN& k, const BS& b, const qcd_point& pt) {
     return acc * Proc::point_norm(pt.gs);
 }
 
+// The same sum over configurations h0, h0 + step, ... below nhel, without the
+// normalisation.
+template <class Proc, typename T, typename KN, typename BS>
+MGRW_HD double helicities_me(const KN& k, const BS& b, const qcd_point& pt, int h0, int step, int nhel) {
+    const auto c = Proc::template couplings<T>(pt.gs, pt.gs2, pt.gk);
+    double acc = 0.0;
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll 1
+#endif
+    for (int h = h0; h < nhel; h += step) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        __asm__ volatile("" ::: "memory");
+#endif
+        typename Proc::template ext<T> w;
+        Proc::template external<T>(b, h, w);
+        cx<T> J[Proc::K];
+        Proc::amplitude(w, k, c, J);
+        acc += double(Proc::colour_sum(J));
+    }
+    return acc;
+}
+
 // ------------------------------------------------ kappa-polynomial form
 //
 // Every diagram of g g -> t tbar + n g carries g^NG kappa^k, k its number of

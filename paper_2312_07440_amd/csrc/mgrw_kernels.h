@@ -112,6 +112,14 @@ __device__ __forceinline__ double reweighted(double w, double me, double me0) {
     return me0 != 0.0 ? w * (me / me0) : __builtin_nan("");
 }
 
+// Sum over groups of L consecutive lanes.
+template <int L>
+__device__ __forceinline__ double group_sum(double v) {
+#pragma unroll
+    for (int o = L / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
 // Per-lane LDS slot with an odd number of 32-bit words, so that lanes reading
 // the same member hit distinct banks.
 template <typename S>
@@ -163,7 +171,8 @@ constexpr int lane_block() {
     }
 }
 
-// One event per lane.  In single precision the per-lane kinematics and
+// One event per lane (large g g -> t tbar batches, or on request).  In single
+// precision the per-lane kinematics and
 // wavefunction bases live in LDS (each lane owns a slot; no barriers); in
 // double precision they stay in registers.
 template <class Proc, typename T>
@@ -191,6 +200,63 @@ qcd_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int6
         Proc::kinematics(p, a.mt, k);
         Proc::external_basis(p, a.mt, b);
         run_points<Proc, T>(k, b, a, n, e, w_in, out, me0_out);
+    }
+}
+
+// Several events per wave, one helicity configuration per lane (processes with
+// fewer than 64 of them).  The first E lanes of a workgroup form the kinematics
+// and bases of its E events in LDS, then every group of NHEL lanes takes an
+// event: all points, the helicity sum across the group.  Against one event per
+// lane, whose slots in LDS allow seven waves per CU: g g -> t tbar g, base + 16
+// points, mixed (150 registers, three waves per SIMD), 262147 events 6.80 ->
+// 4.84 ms, 10^6 events 20.5 -> 18.4; and 5000 events, which are 79 waves of the
+// other kernel, 2.03 -> 0.23 ms.
+// nhel = NHEL, as an argument: the loop over a lane's configurations keeps the
+// program in a basic block of its own, where it rounds as it does in
+// qcd_kernel.
+template <class Proc, typename T, int E>
+__global__ void __launch_bounds__(kBlock)
+qcd_sub_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t n, int nhel, qcd_launch a,
+               double* __restrict__ out, double* __restrict__ me0_out) {
+    constexpr int L = Proc::NHEL;
+    static_assert(L < 64 && 64 % L == 0 && E % (kBlock / L) == 0 && E <= kBlock, "whole groups");
+    using KinT = typename Proc::template kin<T>;
+    using BasT = typename Proc::template basis<T>;
+    __shared__ lds_slot<KinT> ks[E];
+    __shared__ lds_slot<BasT> bs[E];
+    const int64_t first = int64_t(blockIdx.x) * E;
+    if (threadIdx.x < E && first + threadIdx.x < n) {
+        double p[Proc::NEXT][4];
+        load_event<Proc::NEXT>(mom, n, first + threadIdx.x, p);
+        Proc::kinematics(p, a.mt, ks[threadIdx.x].v);
+        Proc::external_basis(p, a.mt, bs[threadIdx.x].v);
+    }
+    __syncthreads();
+    const int sub = threadIdx.x % L;
+#pragma unroll 1
+    for (int i = threadIdx.x / L; i < E; i += kBlock / L) {
+        const int64_t e = first + i;
+        if (e >= n) return;   // whole groups of lanes; no barriers below
+        const KinT& k = ks[i].v;
+        const BasT& b = bs[i].v;
+        const double w = (a.mode == 0 && w_in) ? w_in[e] : 1.0;
+        double me0 = 0.0;
+#pragma unroll 1
+        for (int kp = 0; kp < a.npts; ++kp) {
+            const qcd_point pt = a.pts[kp];
+            double me = group_sum<L>(helicities_me<Proc, T>(k, b, pt, sub, L, nhel)) * Proc::point_norm(pt.gs);
+            if (kp == 0) {
+                me0 = me;
+                if (sub == 0) {
+                    if (a.mode == 1)
+                        out[e] = me;
+                    else if (me0_out)
+                        me0_out[e] = me;
+                }
+            } else if (sub == 0) {
+                out[int64_t(kp - 1) * n + e] = reweighted(w, me, me0);
+            }
+        }
     }
 }
 
@@ -1600,6 +1666,29 @@ hipError_t launch_wave(const double* mom, const double* w_in, int64_t n, const q
         return launch_wave_pipeline<Proc, T, false>(mom, w_in, n, a, out, me0, s);
 }
 
+// Events of a workgroup of qcd_sub_kernel: 32, so that few lanes wait for the
+// kinematics, where that still fills the 768 workgroups that run at once
+// several times; below, what the workgroup's lanes hold at once.
+constexpr int kSubTile = 32;
+constexpr int64_t kSubEvents = 196608;
+// Events from which on g g -> t tbar, whose 385 operations per configuration
+// weigh little against a cross-lane sum per point, runs one event per lane:
+// 2^20 events 2.07 ms against 2.27, in double precision 500000 events 1.70
+// against 1.97; below, a round of that kernel's waves is not full (100000
+// events: 303 us against 239).
+constexpr int64_t lane_events(int fp64) { return fp64 ? 106496 : 126976; }
+template <class Proc, int E>
+void launch_sub(int fp64, const double* mom, const double* w_in, int64_t n, const qcd_launch& a, double* out,
+                double* me0, hipStream_t s) {
+    const dim3 grid(unsigned((n + E - 1) / E));
+    if (fp64)
+        hipLaunchKernelGGL((qcd_sub_kernel<Proc, double, E>), grid, dim3(kBlock), 0, s, mom, w_in, n, int(Proc::NHEL),
+                           a, out, me0);
+    else
+        hipLaunchKernelGGL((qcd_sub_kernel<Proc, float, E>), grid, dim3(kBlock), 0, s, mom, w_in, n, int(Proc::NHEL),
+                           a, out, me0);
+}
+
 template <class Proc>
 hipError_t launch_main(int fp64, const double* mom, const double* w_in, int64_t n, const qcd_launch& a,
                        double* out, double* me0, hipStream_t s) {
@@ -1609,6 +1698,18 @@ hipError_t launch_main(int fp64, const double* mom, const double* w_in, int64_t 
     if (a.mapping == MGRW_MAP_EVENT_PER_WAVE)
         return fp64 ? launch_wave<Proc, double>(mom, w_in, n, a, out, me0, s)
                     : launch_wave<Proc, float>(mom, w_in, n, a, out, me0, s);
+    if constexpr (Proc::NHEL < 64) {
+        if (a.mapping == MGRW_MAP_AUTO && !(Proc::NG <= 2 && n >= lane_events(fp64))) {
+            constexpr int G = kBlock / Proc::NHEL;   // events a workgroup's lanes hold at once
+            mark(a.t0, s);
+            if (n >= kSubEvents)
+                launch_sub<Proc, kSubTile>(fp64, mom, w_in, n, a, out, me0, s);
+            else
+                launch_sub<Proc, G>(fp64, mom, w_in, n, a, out, me0, s);
+            mark(a.t1, s);
+            return hipGetLastError();
+        }
+    }
     constexpr int NBD = lane_block<Proc, double>(), NBF = lane_block<Proc, float>();
     mark(a.t0, s);
     if (fp64)

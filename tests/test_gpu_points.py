@@ -142,3 +142,30 @@ def test_buffers_survive_handles_and_streams(torch_dev):
         p.close()
     torch.cuda.synchronize()
     assert all(torch.equal(o, ref) for o in outs)
+
+
+# one event per lane and several events per wave sum the same helicity terms in
+# another order, in double: NHEL rounding errors per |M|^2, three of those in a
+# weight; in double precision the terms themselves are held to 1e-12
+SUM_TOL = {"mixed": 3 * 32 * 2.0 ** -53, "fp64": FP64_TOL}
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("proc,n", [("gg_tt", 1), ("gg_tt", 15), ("gg_tt", 17), ("gg_tt", 106495), ("gg_tt", 126976),
+                                    ("gg_ttg", 1), ("gg_ttg", 7), ("gg_ttg", 9), ("gg_ttg", 196607),
+                                    ("gg_ttg", 196613)])
+def test_several_events_per_wave(torch_dev, prec, proc, n):
+    import paper_2312_07440_amd as mg
+    torch = torch_dev
+    mom = torch.from_numpy(generate_events(proc, min(n, 4099), first_event=11)).cuda()
+    mom = mom.repeat(1, 1, -(-n // mom.shape[2]))[:, :, :n].contiguous()
+    w_in = torch.linspace(0.5, 2.0, n, dtype=torch.float64, device="cuda")
+    got, me = [], []
+    for mapping in ("auto", "event_per_lane"):
+        p = mg.Process(proc, prec)
+        p.set_params([{"kappa_ttg": float(k), "alphas": 0.12} for k in kappa_points(3)])
+        p.set_lane_mapping(mapping)
+        got.append(p.reweight(mom, w_in=w_in))
+        me.append(p.eval_me(mom, point=1))
+    assert (got[0] / got[1] - 1).abs().max() <= SUM_TOL[prec]
+    assert (me[0] / me[1] - 1).abs().max() <= SUM_TOL[prec]
