@@ -88,16 +88,17 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def flops_per_event(proc, n_points_total, n_hel):
+def flops_per_event(proc, n_points_total, n_hel, prec="mixed"):
     path = os.path.join(HERE, "paper_2312_07440_amd", "csrc", "gen", "flops.json")
     f = json.load(open(path))[proc]
     n_hel = f.get("evaluated_helicities", n_hel)
     per = f["per_helicity_flops"]
-    if n_hel == 64 and "external_flops" in f:
-        # one block of 64 configurations per wave: the external wavefunctions
-        # are assembled once per event, not once per point
-        ext = f["external_flops"]
-        return n_hel * (n_points_total * (per - ext) + ext), f
+    q = f.get(f"pass_{prec}")
+    if q and n_points_total > 1:
+        # several points a pass: the chains once per pass, the rest at every
+        # point; the external wavefunctions once per event
+        passes = -(-n_points_total // q["points"])
+        return n_hel * (passes * q["shared_flops"] + n_points_total * q["point_flops"]) + f["external_flops"] * n_hel, f
     return n_points_total * n_hel * per, f
 
 
@@ -393,7 +394,7 @@ def main():
         f"{['%.1f' % x for x in amp_ms]}, wall {wall:.2f}s")
 
     n_total_points = args.points + 1
-    fpe, fcounts = flops_per_event(args.proc, n_total_points, proc.n_hel)
+    fpe, fcounts = flops_per_event(args.proc, n_total_points, proc.n_hel, args.prec)
     # the amplitude kernel skips the events left to the FP64 re-evaluation
     # (outside the timed interval): count only the events it evaluates
     tau = proc.rescue_threshold if args.proc != "ee_5a" else 0.0
@@ -431,8 +432,8 @@ def main():
                      "kernel_ms": kms,
                      "flops_per_event": fpe, "per_helicity_flops": fcounts["per_helicity_flops"],
                      "events_evaluated": n_eval, "events_rescued_fp64": n_rescued, "rescue_tau": tau,
-                     "counts": "algorithmic flops of the generated program (currents rebuilt per closing "
-                               "group included) x the events the timed kernel evaluates",
+                     "counts": "algorithmic flops of the generated program, the chains once per pass over "
+                               "several points, x the events the timed kernel evaluates",
                      "frac_executed": None if exec_ratio is None else exec_ratio * achieved / peak},
     }
     if not args.no_end_to_end:

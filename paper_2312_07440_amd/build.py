@@ -82,6 +82,14 @@ def write_flops():
                      "per_helicity_flops": c[0] + c[1],
                      "colour_sum_flops": c[2] + c[3], "external_flops": c[4] + c[5]}
         lib.mgrw_host_kpoly_flops.restype = ctypes.c_longlong
+        # kernels that take several points a pass: the part of the operations
+        # that the pass shares and the part that every point adds
+        lib.mgrw_host_pass_flops.restype = ctypes.c_longlong
+        for prec, fp64, points in (("mixed", 0, 2), ("fp64", 1, 3)):
+            one, two = (lib.mgrw_host_pass_flops(ng, m, fp64) for m in (1, 2))
+            if two > 0:
+                out[name][f"pass_{prec}"] = {"points": points, "shared_flops": 2 * one - two,
+                                             "point_flops": two - one}
         kf = lib.mgrw_host_kpoly_flops(ng)
         if kf > 0:
             out[name]["kpoly_per_helicity_flops"] = kf

@@ -18,21 +18,46 @@
 
 namespace {
 
-struct cfloat {
+// S: counts as the double-precision programs do (points share the t tbar
+// current of their root closures).
+template <bool S>
+struct counting {
     double v;
     static thread_local long long n_add, n_mul;
-    cfloat() = default;
-    constexpr cfloat(double x) : v(x) {}
+    counting() = default;
+    constexpr counting(double x) : v(x) {}
     explicit operator double() const { return v; }
 };
-thread_local long long cfloat::n_add = 0;
-thread_local long long cfloat::n_mul = 0;
+template <bool S> thread_local long long counting<S>::n_add = 0;
+template <bool S> thread_local long long counting<S>::n_mul = 0;
+using cfloat = counting<false>;
+using cdouble = counting<true>;
 
-inline cfloat operator+(cfloat a, cfloat b) { ++cfloat::n_add; return {a.v + b.v}; }
-inline cfloat operator-(cfloat a, cfloat b) { ++cfloat::n_add; return {a.v - b.v}; }
-inline cfloat operator*(cfloat a, cfloat b) { ++cfloat::n_mul; return {a.v * b.v}; }
-inline cfloat operator-(cfloat a) { return {-a.v}; }
-inline bool operator>(cfloat a, cfloat b) { return a.v > b.v; }
+template <bool S> counting<S> operator+(counting<S> a, counting<S> b) { ++counting<S>::n_add; return {a.v + b.v}; }
+template <bool S> counting<S> operator-(counting<S> a, counting<S> b) { ++counting<S>::n_add; return {a.v - b.v}; }
+template <bool S> counting<S> operator*(counting<S> a, counting<S> b) { ++counting<S>::n_mul; return {a.v * b.v}; }
+template <bool S> counting<S> operator-(counting<S> a) { return {-a.v}; }
+template <bool S> bool operator>(counting<S> a, counting<S> b) { return a.v > b.v; }
+
+}  // namespace
+namespace mgrw {
+template <> struct shared_root<cdouble> : std::true_type {};
+}  // namespace mgrw
+namespace {
+
+// Flows of M points, for counting a pass over several points.
+template <typename T, int K, int M>
+struct count_acc {
+    mgrw::cx<T> J[M][K];
+};
+template <int I, typename T, int K, int M>
+void jadd(count_acc<T, K, M>& J, const mgrw::cm<T, M>& s) {
+    for (int m = 0; m < M; ++m) J.J[m][I] = J.J[m][I] + s.v[m];
+}
+template <int I, typename T, int K, int M>
+void jsub(count_acc<T, K, M>& J, const mgrw::cm<T, M>& s) {
+    for (int m = 0; m < M; ++m) J.J[m][I] = J.J[m][I] - s.v[m];
+}
 
 template <class Proc, typename T>
 void me_events(const double* mom, int64_t n, double mt, const mgrw::qcd_point* pts, int npts, double* me) {
@@ -140,6 +165,28 @@ void count_ops(long long* counts) {
     counts[1] = cfloat::n_mul;
 }
 
+// add + mul of one helicity configuration of a pass over M points: chains,
+// closures, flows and colour sums, without the external wavefunctions.
+template <class Proc, typename T, int M>
+long long count_pass() {
+    double p[Proc::NEXT][4];
+    for (int i = 0; i < Proc::NEXT; ++i)
+        for (int m = 0; m < 4; ++m) p[i][m] = 1.0 + i + 0.25 * m;
+    typename Proc::template kin<T> k;
+    Proc::kinematics(p, 173.0, k);
+    typename Proc::template basis<T> b;
+    Proc::external_basis(p, 173.0, b);
+    typename Proc::template ext<T> w;
+    Proc::external(b, 5, w);
+    const mgrw::qcd_point pt[M] = {};
+    const auto c = mgrw::couplings_of<Proc, T, M>(pt, 0, M);
+    count_acc<T, Proc::K, M> J;
+    T::n_add = T::n_mul = 0;
+    Proc::template program<T>(w, k, c, J);
+    for (int m = 0; m < M; ++m) (void)Proc::colour_sum(J.J[m]);
+    return T::n_add + T::n_mul;
+}
+
 }  // namespace
 
 extern "C" {
@@ -189,6 +236,19 @@ int mgrw_host_qcd_me_split(int ng, const double* mom, int64_t n, double mt, cons
     }
     me_events_split<mgrw::gg_ttggg>(mom, n, mt, pts, npts, me);
     return 0;
+}
+
+// g g -> t tbar g g: a pass over `points` (1 to 3) points, as the single (0) or
+// double (1) precision program evaluates it.
+long long mgrw_host_pass_flops(int ng, int points, int fp64) {
+    if (ng != 4) return -1;
+    using P = mgrw::gg_ttgg;
+    switch (points) {
+        case 1: return fp64 ? count_pass<P, cdouble, 1>() : count_pass<P, cfloat, 1>();
+        case 2: return fp64 ? count_pass<P, cdouble, 2>() : count_pass<P, cfloat, 2>();
+        case 3: return fp64 ? count_pass<P, cdouble, 3>() : -1;
+        default: return -1;
+    }
 }
 
 long long mgrw_host_kpoly_flops(int ng) {

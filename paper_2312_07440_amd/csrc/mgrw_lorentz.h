@@ -438,45 +438,46 @@ MGRW_HD v4<T> tt_current(const sp<T>& ub, const sp<T>& v, T coup, T iP) {
 // current, so that its root closures round as they do for one point alone;
 // in double precision the points share the current without their coupling,
 // which multiplies the closed vertex instead.
-template <int M>
+template <typename T> struct shared_root : std::false_type {};
+template <> struct shared_root<double> : std::true_type {};
+template <typename T, int M, bool S = shared_root<T>::value>
 struct ttk {
-    v4<float> v[M];
+    v4<T> v[M];
 };
-template <int M>
-struct ttk_shared {
-    v4<double> v;
-    rm<double, M> coup;
+template <typename T, int M>
+struct ttk<T, M, true> {
+    v4<T> v;
+    rm<T, M> coup;
 };
-template <int M, int... m>
-MGRW_HD ttk<M> tt_points(const sp<float>& ub, const sp<float>& v, const rm<float, M>& coup, float iP,
-                         std::integer_sequence<int, m...>) {
+template <typename T, int M, int... m>
+MGRW_HD ttk<T, M> tt_points(const sp<T>& ub, const sp<T>& v, const rm<T, M>& coup, T iP,
+                            std::integer_sequence<int, m...>) {
     return {{tt_current(ub, v, coup.v[m], iP)...}};
 }
-template <int M>
-MGRW_HD ttk<M> tt_current(const sp<float>& ub, const sp<float>& v, const rm<float, M>& coup, float iP) {
-    return tt_points(ub, v, coup, iP, points_seq<M>{});
-}
-template <int M>
-MGRW_HD ttk_shared<M> tt_current(const sp<double>& ub, const sp<double>& v, const rm<double, M>& coup, double iP) {
-    return {tt_current(ub, v, 1.0, iP), coup};
+template <typename T, int M>
+MGRW_HD ttk<T, M> tt_current(const sp<T>& ub, const sp<T>& v, const rm<T, M>& coup, T iP) {
+    if constexpr (shared_root<T>::value)
+        return {tt_current(ub, v, T(1.0), iP), coup};
+    else
+        return tt_points(ub, v, coup, iP, points_seq<M>{});
 }
 
 // Root closures on the t tbar current K of one point or of M points (at most
 // two in single precision): macros, so that every point's closure is a call
 // in the program itself and rounds as in the program for one point (see rm).
 template <typename T> MGRW_HD const v4<T>& root_at(const v4<T>& K, int) { return K; }
-template <int M> MGRW_HD const v4<float>& root_at(const ttk<M>& K, int m) { return K.v[m]; }
-template <int M> MGRW_HD const v4<double>& root_at(const ttk_shared<M>& K, int) { return K.v; }
+template <typename T, int M> MGRW_HD const v4<T>& root_at(const ttk<T, M, false>& K, int m) { return K.v[m]; }
+template <typename T, int M> MGRW_HD const v4<T>& root_at(const ttk<T, M, true>& K, int) { return K.v; }
 template <typename K> struct root_points { static constexpr int n = 1; };
-template <int M> struct root_points<const ttk<M>> { static constexpr int n = M; };
+template <typename T, int M> struct root_points<const ttk<T, M, false>> { static constexpr int n = M; };
 template <typename T> MGRW_HD cx<T> root_value(const v4<T>&) { return {}; }
-template <int M> MGRW_HD cm<float, M> root_value(const ttk<M>&) { return {}; }
-template <int M> MGRW_HD cx<double> root_value(const ttk_shared<M>&) { return {}; }
+template <typename T, int M> MGRW_HD cm<T, M> root_value(const ttk<T, M, false>&) { return {}; }
+template <typename T, int M> MGRW_HD cx<T> root_value(const ttk<T, M, true>&) { return {}; }
 template <typename T> MGRW_HD void root_put(cx<T>& a, int, cx<T> x) { a = x; }
 template <typename T, int M> MGRW_HD void root_put(cm<T, M>& a, int m, cx<T> x) { a.v[m] = x; }
 template <typename T> MGRW_HD cx<T> root_done(const v4<T>&, cx<T> a) { return a; }
-template <int M> MGRW_HD const cm<float, M>& root_done(const ttk<M>&, const cm<float, M>& a) { return a; }
-template <int M> MGRW_HD cm<double, M> root_done(const ttk_shared<M>& K, cx<double> a) { return a * K.coup; }
+template <typename T, int M> MGRW_HD const cm<T, M>& root_done(const ttk<T, M, false>&, const cm<T, M>& a) { return a; }
+template <typename T, int M> MGRW_HD cm<T, M> root_done(const ttk<T, M, true>& K, cx<T> a) { return a * K.coup; }
 template <typename V>
 struct root_parts {
     V A, B, C;
