@@ -30,6 +30,10 @@
  *    three library-owned streams of the device (default priority, created on
  *    first use, kept until the process ends), forked from and joined back
  *    into `stream` with events, so the call stays ordered on `stream`.
+ *  - Intermediate buffers are stream-ordered allocations from a memory pool of
+ *    the library's own (one per device), which keeps up to 12 GiB across
+ *    synchronisations and gives its memory back when the last process handle is
+ *    destroyed; under stream capture they come from the default pool.
  *  - Return values are mgrw_status codes; on a non-OK status the calling
  *    thread's mgrw_last_error() describes it.  No exception crosses the ABI.
  *  - A process handle is not thread-safe; distinct handles are independent.
@@ -122,8 +126,9 @@ mgrw_status mgrw_eval_me(mgrw_process *p, const double *mom, int64_t n_events, i
  *   w_out[k*n_events + e] = W_e * (|M_k|^2 / |M_base|^2),
  * W_e = w_in[e] (device float64[n_events]) or 1 when w_in is NULL; quiet NaN
  * where |M_base|^2 = 0 (eq. (3) requires |M|^2 != 0).  me_base_out (device
- * float64[n_events], may be NULL) receives |M_base|^2.  All points are
- * evaluated in full inside one kernel, so momenta are read once.
+ * float64[n_events], may be NULL) receives |M_base|^2.  Momenta are read once
+ * for all points; chains that hold no parameter are formed once for several
+ * points, couplings, flows, colour and helicity sums at every point.
  * Errors: as mgrw_eval_me; MGRW_ERR_STATE when no points are set. */
 mgrw_status mgrw_reweight(mgrw_process *p, const double *mom, const double *w_in, int64_t n_events,
                           double *w_out, double *me_base_out, void *stream);
@@ -134,7 +139,7 @@ mgrw_status mgrw_reweight(mgrw_process *p, const double *mom, const double *w_in
  * per-event kinematics records and the list of events for the FP64
  * re-evaluation come from a 256 MiB device array inside the library (one per
  * GPU, held until the process ends); the events run in chunks whose buffers
- * fit it (about 2.5e5 events per chunk for g g -> t tbar g g).  The call
+ * fit it (about 1e5 events per chunk for g g -> t tbar g g).  The call
  * allocates nothing and records no kernel timing (mgrw_kernel_time_ms then
  * reports MGRW_ERR_STATE).  Every call on a GPU shares that GPU's array, so
  * calls that overlap on one GPU (other streams, other threads, other handles)
@@ -181,7 +186,9 @@ mgrw_status mgrw_process_info(const mgrw_process *p, int *n_ext, int *n_flows, i
                               int *n_diagrams);
 
 /* Options.  MGRW_OPT_LANE_MAPPING selects how events map onto the GPU's
- * lanes for the exact QCD kernels: MGRW_MAP_AUTO (default),
+ * lanes for the exact QCD kernels: MGRW_MAP_AUTO (default:
+ * several events per wave where the configurations do not fill one, else one
+ * per wave; large g g -> t tbar batches one per lane),
  * MGRW_MAP_EVENT_PER_LANE (one event per lane, helicities in a loop), or
  * MGRW_MAP_EVENT_PER_WAVE (one event per 64-lane wave, helicity
  * configurations on the lanes; processes with a multiple of 64 helicity
