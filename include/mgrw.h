@@ -129,6 +129,9 @@ mgrw_status mgrw_eval_me(mgrw_process *p, const double *mom, int64_t n_events, i
  * float64[n_events], may be NULL) receives |M_base|^2.  Momenta are read once
  * for all points; chains that hold no parameter are formed once for several
  * points, couplings, flows, colour and helicity sums at every point.
+ * g g -> t tbar: the number of events selects one of two kernels (see
+ * MGRW_OPT_LANE_MAPPING), which agree to double rounding; for every other
+ * process an event's result does not depend on the batch it is in.
  * Errors: as mgrw_eval_me; MGRW_ERR_STATE when no points are set. */
 mgrw_status mgrw_reweight(mgrw_process *p, const double *mom, const double *w_in, int64_t n_events,
                           double *w_out, double *me_base_out, void *stream);
@@ -254,7 +257,8 @@ void mgrw_destroy_process(mgrw_process *p);
  * n_ext_max momentum rows per event, mom[(i*4+mu)*N + e], of which a process
  * with n_ext particles reads rows 0..n_ext-1 in its own particle order.
  * w_out [P][N] and me_base_out (nullable) as in mgrw_reweight; each event's
- * results are those mgrw_reweight gives for it with its process's handle.
+ * results are those mgrw_reweight gives for it with its process's handle in a
+ * batch of that process's events.
  * The events of each process are gathered into a contiguous batch on the
  * device and reweighted there; the call synchronises the stream once, to
  * read the per-process counts.  Errors: MGRW_ERR_ARG (sizes, differing P,

@@ -135,10 +135,11 @@ mgrw_status launched(hipError_t err) {
 
 // Shared body of eval_me (mode 1, one point) and reweight (mode 0).  With a
 // scratch span the launch allocates nothing (its buffers come from the span)
-// and records no kernel timing.
+// and records no kernel timing.  whole > 0: the n events are a piece of a batch
+// of that many, by which the kernel is chosen.
 mgrw_status run(mgrw_process* p, const double* mom, const double* w_in, int64_t n, const mgrw_params* pts,
                 int npts, int mode, double* out, double* me0, void* stream, int kpoly = 0,
-                scratch_span sc = {nullptr, 0}) {
+                scratch_span sc = {nullptr, 0}, int64_t whole = 0) {
     if (n < 0) return fail(MGRW_ERR_ARG, "n_events < 0");
     if (n == 0) return MGRW_OK;
     const hipEvent_t t0 = sc.ptr ? nullptr : p->t0, t1 = sc.ptr ? nullptr : p->t1;
@@ -188,6 +189,7 @@ mgrw_status run(mgrw_process* p, const double* mom, const double* w_in, int64_t 
     // whole waves; the others choose by the batch (launch_main)
     a.mapping = p->mapping != MGRW_MAP_AUTO ? p->mapping
                 : (info_of(p->proc).n_hel % 64 == 0 ? MGRW_MAP_EVENT_PER_WAVE : MGRW_MAP_AUTO);
+    a.batch = whole > 0 ? whole : n;
     a.kpoly = kpoly;
     a.rescue_tau = p->rescue_tau;
     a.colour_mfma = p->colour_mfma;
@@ -327,12 +329,7 @@ mgrw_status mgrw_eval_me(mgrw_process* p, const double* mom, int64_t n_events, i
 
 mgrw_status mgrw_reweight(mgrw_process* p, const double* mom, const double* w_in, int64_t n_events,
                           double* w_out, double* me_base_out, void* stream) {
-    if (!p) return fail(MGRW_ERR_ARG, "process is NULL");
-    if (p->n_points == 0) return fail(MGRW_ERR_STATE, "no parameter points set");
-    mgrw_params all[kMaxLaunchPoints];
-    all[0] = p->base;
-    for (int k = 0; k < p->n_points; ++k) all[k + 1] = p->points[k];
-    return run(p, mom, w_in, n_events, all, p->n_points + 1, 0, w_out, me_base_out, stream);
+    return reweight_piece(p, mom, w_in, n_events, w_out, me_base_out, stream, n_events);
 }
 
 mgrw_status mgrw_reweight_kpoly(mgrw_process* p, const double* mom, const double* w_in, int64_t n_events,
@@ -447,6 +444,16 @@ const char* mgrw_last_error(void) { return g_last_error.c_str(); }
 }  // extern "C"
 
 mgrw_status mgrw::set_error(mgrw_status code, const std::string& msg) { return fail(code, msg); }
+
+mgrw_status mgrw::reweight_piece(mgrw_process* p, const double* mom, const double* w_in, int64_t n, double* w_out,
+                                 double* me_base_out, void* stream, int64_t whole) {
+    if (!p) return fail(MGRW_ERR_ARG, "process is NULL");
+    if (p->n_points == 0) return fail(MGRW_ERR_STATE, "no parameter points set");
+    mgrw_params all[kMaxLaunchPoints];
+    all[0] = p->base;
+    for (int k = 0; k < p->n_points; ++k) all[k + 1] = p->points[k];
+    return run(p, mom, w_in, n, all, p->n_points + 1, 0, w_out, me_base_out, stream, 0, {nullptr, 0}, whole);
+}
 
 mgrw_status mgrw::check_device_ptr(const void* ptr, const char* what, bool allow_null) {
     if (!ptr) {

@@ -16,6 +16,10 @@ mgrw_status set_error(mgrw_status code, const std::string& msg);
 // MGRW_OK if ptr is device (or managed) memory, or NULL with allow_null;
 // else MGRW_ERR_ARG naming `what`.
 mgrw_status check_device_ptr(const void* ptr, const char* what, bool allow_null);
+// mgrw_reweight of n events that are a piece of a batch of `whole`: the kernel
+// is chosen by the batch, so that each event gets the whole call's result.
+mgrw_status reweight_piece(mgrw_process* p, const double* mom, const double* w_in, int64_t n, double* w_out,
+                           double* me_base_out, void* stream, int64_t whole);
 }  // namespace mgrw
 
 struct mgrw_process {

@@ -43,7 +43,8 @@ struct qcd_launch {
     int npts;        // points in pts (base first)
     int mode;        // 0: reweight, 1: |M|^2 of pts[0] only
     double mt;
-    int mapping;     // MGRW_MAP_EVENT_PER_LANE or MGRW_MAP_EVENT_PER_WAVE
+    int mapping;     // MGRW_MAP_EVENT_PER_LANE or MGRW_MAP_EVENT_PER_WAVE; MGRW_MAP_AUTO: chosen by `batch`
+    int64_t batch;   // events of the whole call (the launch may be a piece of it)
     int kpoly;       // 1: kappa-polynomial evaluation (one program per helicity for all points)
     double rescue_tau;   // > 0: events with a gluon invariant |2 p_i.p_j|/s below it are redone in FP64
     hipEvent_t t0, t1;   // non-null: recorded around the amplitude kernel(s) of the launch
@@ -1714,10 +1715,10 @@ hipError_t launch_main(int fp64, const double* mom, const double* w_in, int64_t 
         return fp64 ? launch_wave<Proc, double>(mom, w_in, n, a, out, me0, s)
                     : launch_wave<Proc, float>(mom, w_in, n, a, out, me0, s);
     if constexpr (Proc::NHEL < 64) {
-        if (a.mapping == MGRW_MAP_AUTO && !(Proc::NG <= 2 && n >= lane_events(fp64))) {
+        if (a.mapping == MGRW_MAP_AUTO && !(Proc::NG <= 2 && a.batch >= lane_events(fp64))) {
             constexpr int G = kBlock / Proc::NHEL;   // events a workgroup's lanes hold at once
             mark(a.t0, s);
-            if (n >= kSubEvents)
+            if (a.batch >= kSubEvents)
                 launch_sub<Proc, kSubTile>(fp64, mom, w_in, n, a, out, me0, s);
             else
                 launch_sub<Proc, G>(fp64, mom, w_in, n, a, out, me0, s);

@@ -105,7 +105,7 @@ extern "C" mgrw_status mgrw_reweight_host(mgrw_process* p, const double* mom, co
         hipError_t err = hipMemcpy2DAsync(mom_d, w, mom + e0, row, w, size_t(n_ext) * 4, hipMemcpyHostToDevice, s);
         if (err == hipSuccess && w_in) err = hipMemcpyAsync(w_d, w_in + e0, w, hipMemcpyHostToDevice, s);
         if (err != hipSuccess) return drain(dev_fail(err));
-        st = mgrw_reweight(p, mom_d, w_in ? w_d : nullptr, m, out_d, me_base_out ? me0_d : nullptr, s);
+        st = mgrw::reweight_piece(p, mom_d, w_in ? w_d : nullptr, m, out_d, me_base_out ? me0_d : nullptr, s, n_events);
         if (st != MGRW_OK) return drain(st);
         err = hipMemcpy2DAsync(w_out + e0, row, out_d, w, w, size_t(P), hipMemcpyDeviceToHost, s);
         if (err == hipSuccess && me_base_out) err = hipMemcpyAsync(me_base_out + e0, me0_d, w, hipMemcpyDeviceToHost, s);
