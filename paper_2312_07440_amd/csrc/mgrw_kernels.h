@@ -16,6 +16,8 @@ namespace mgrw {
 
 constexpr int kBlock = 256;
 constexpr int kMaxLaunchPoints = MGRW_MAX_POINTS + 1;   // base + new points
+// Workgroups of one launch: HIP takes fewer than 2^32 threads in x.
+constexpr int64_t kLaunchBlocks = (int64_t(1) << 32) / kBlock - 1;
 
 // Device memory a launch may use for its intermediate buffers instead of
 // allocating them.  ptr == nullptr: the launch allocates (stream-ordered).
@@ -214,11 +216,11 @@ qcd_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int6
 // other kernel, 2.03 -> 0.23 ms.
 // nhel = NHEL, as an argument: the loop over a lane's configurations keeps the
 // program in a basic block of its own, where it rounds as it does in
-// qcd_kernel.
+// qcd_kernel.  Events 0 .. nb - 1 from the pointers on, whose rows are n apart.
 template <class Proc, typename T, int E>
 __global__ void __launch_bounds__(kBlock)
-qcd_sub_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t n, int nhel, qcd_launch a,
-               double* __restrict__ out, double* __restrict__ me0_out) {
+qcd_sub_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t nb, int64_t n, int nhel,
+               qcd_launch a, double* __restrict__ out, double* __restrict__ me0_out) {
     constexpr int L = Proc::NHEL;
     static_assert(L < 64 && 64 % L == 0 && E % (kBlock / L) == 0 && E <= kBlock, "whole groups");
     using KinT = typename Proc::template kin<T>;
@@ -226,7 +228,7 @@ qcd_sub_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, 
     __shared__ lds_slot<KinT> ks[E];
     __shared__ lds_slot<BasT> bs[E];
     const int64_t first = int64_t(blockIdx.x) * E;
-    if (threadIdx.x < E && first + threadIdx.x < n) {
+    if (threadIdx.x < E && first + threadIdx.x < nb) {
         double p[Proc::NEXT][4];
         load_event<Proc::NEXT>(mom, n, first + threadIdx.x, p);
         Proc::kinematics(p, a.mt, ks[threadIdx.x].v);
@@ -237,7 +239,7 @@ qcd_sub_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, 
 #pragma unroll 1
     for (int i = threadIdx.x / L; i < E; i += kBlock / L) {
         const int64_t e = first + i;
-        if (e >= n) return;   // whole groups of lanes; no barriers below
+        if (e >= nb) return;   // whole groups of lanes; no barriers below
         const KinT& k = ks[i].v;
         const BasT& b = bs[i].v;
         const double w = (a.mode == 0 && w_in) ? w_in[e] : 1.0;
@@ -1693,16 +1695,16 @@ constexpr int64_t kSubEvents = 196608;
 // against 1.97; below, a round of that kernel's waves is not full (100000
 // events: 303 us against 239).
 constexpr int64_t lane_events(int fp64) { return fp64 ? 106496 : 126976; }
+// A launch holds kLaunchBlocks E events: 2^29 of g g -> t tbar g.
 template <class Proc, int E>
 void launch_sub(int fp64, const double* mom, const double* w_in, int64_t n, const qcd_launch& a, double* out,
                 double* me0, hipStream_t s) {
-    const dim3 grid(unsigned((n + E - 1) / E));
-    if (fp64)
-        hipLaunchKernelGGL((qcd_sub_kernel<Proc, double, E>), grid, dim3(kBlock), 0, s, mom, w_in, n, int(Proc::NHEL),
-                           a, out, me0);
-    else
-        hipLaunchKernelGGL((qcd_sub_kernel<Proc, float, E>), grid, dim3(kBlock), 0, s, mom, w_in, n, int(Proc::NHEL),
-                           a, out, me0);
+    const auto kernel = fp64 ? qcd_sub_kernel<Proc, double, E> : qcd_sub_kernel<Proc, float, E>;
+    for (int64_t e0 = 0; e0 < n; e0 += kLaunchBlocks * E) {
+        const int64_t nb = n - e0 < kLaunchBlocks * E ? n - e0 : kLaunchBlocks * E;
+        hipLaunchKernelGGL(kernel, dim3(unsigned((nb + E - 1) / E)), dim3(kBlock), 0, s, mom + e0,
+                           w_in ? w_in + e0 : nullptr, nb, n, int(Proc::NHEL), a, out + e0, me0 ? me0 + e0 : nullptr);
+    }
 }
 
 template <class Proc>

@@ -42,3 +42,27 @@ def test_host_chunks_equal_the_device_call(torch_dev, prec, proc, n, chunk):
     p = handle(proc, prec)
     ref = p.reweight(torch.from_numpy(mom).cuda(), w_in=torch.from_numpy(w).cuda()).cpu().numpy()
     assert np.array_equal(p.reweight_host(mom, w_in=w, chunk=chunk), ref)
+
+
+def test_more_events_than_one_launch_holds(torch_dev):
+    """g g -> t tbar g, several threads per event: 2^29 events are 2^32 threads,
+    which one launch does not take."""
+    torch = torch_dev
+    n = (1 << 29) + 33
+    if torch.cuda.mem_get_info()[0] < 130 << 30:
+        pytest.skip("needs 130 GiB of free device memory")
+    base = torch.from_numpy(generate_events("gg_ttg", 4099, first_event=11)).cuda()
+    p = handle("gg_ttg", "mixed")
+    ref = p.eval_me(base)
+    reps = -(-n // 4099)
+    mom = torch.empty(5, 4, n, dtype=torch.float64, device="cuda")
+    for i in range(5):
+        for mu in range(4):
+            mom[i, mu] = base[i, mu].repeat(reps)[:n]
+    out = torch.full((n,), -1.0, dtype=torch.float64, device="cuda")
+    p.eval_me(mom, out=out)
+    whole = n // 4099 * 4099
+    assert bool((out[:whole].view(-1, 4099) == ref).all())
+    assert torch.equal(out[whole:], ref[: n - whole])
+    del mom, out
+    torch.cuda.empty_cache()
