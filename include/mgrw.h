@@ -132,6 +132,9 @@ mgrw_status mgrw_eval_me(mgrw_process *p, const double *mom, int64_t n_events, i
  * g g -> t tbar: the number of events selects one of two kernels (see
  * MGRW_OPT_LANE_MAPPING), which agree to double rounding; for every other
  * process an event's result does not depend on the batch it is in.
+ * Weights in place: w_in may be a row of w_out or be me_base_out (here, in
+ * mgrw_reweight_noalloc and in mgrw_reweight_kpoly); the arrays must not
+ * overlap in any other way.
  * Errors: as mgrw_eval_me; MGRW_ERR_STATE when no points are set. */
 mgrw_status mgrw_reweight(mgrw_process *p, const double *mom, const double *w_in, int64_t n_events,
                           double *w_out, double *me_base_out, void *stream);

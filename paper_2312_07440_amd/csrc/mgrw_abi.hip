@@ -61,8 +61,8 @@ ee_mumu_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, 
         out[e] = me0;
         return;
     }
+    const double w = w_in ? w_in[e] : 1.0;   // before me0_out, which may be the same array
     if (me0_out) me0_out[e] = me0;
-    const double w = w_in ? w_in[e] : 1.0;
     for (int k = 1; k < a.npts; ++k) out[int64_t(k - 1) * n + e] = reweighted(w, ev.me(a.pts[k]), me0);
 }
 
@@ -186,7 +186,7 @@ mgrw_status run(mgrw_process* p, const double* mom, const double* w_in, int64_t 
     a.mode = mode;
     a.mt = p->base.mt;
     // automatic choice: one event per wave when the helicity configurations fill
-    // whole waves; the others choose by the batch (launch_main)
+    // whole waves; the others choose by the batch (launch_lane_kernels)
     a.mapping = p->mapping != MGRW_MAP_AUTO ? p->mapping
                 : (info_of(p->proc).n_hel % 64 == 0 ? MGRW_MAP_EVENT_PER_WAVE : MGRW_MAP_AUTO);
     a.batch = whole > 0 ? whole : n;

@@ -177,14 +177,15 @@ constexpr int lane_block() {
 // One event per lane (large g g -> t tbar batches, or on request).  In single
 // precision the per-lane kinematics and
 // wavefunction bases live in LDS (each lane owns a slot; no barriers); in
-// double precision they stay in registers.
+// double precision they stay in registers.  Events 0 .. nb - 1 from the
+// pointers on, whose rows are n apart.
 template <class Proc, typename T>
 __global__ void __launch_bounds__((lane_block<Proc, T>()))
-qcd_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t n, qcd_launch a,
+qcd_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t nb, int64_t n, qcd_launch a,
            double* __restrict__ out, double* __restrict__ me0_out) {
     constexpr int NB = lane_block<Proc, T>();
     const int64_t e = int64_t(blockIdx.x) * NB + threadIdx.x;
-    if (e >= n) return;   // no barriers below: early exit is safe
+    if (e >= nb) return;   // no barriers below: early exit is safe
     double p[Proc::NEXT][4];
     load_event<Proc::NEXT>(mom, n, e, p);
     using KinT = typename Proc::template kin<T>;
@@ -216,7 +217,7 @@ qcd_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int6
 // other kernel, 2.03 -> 0.23 ms.
 // nhel = NHEL, as an argument: the loop over a lane's configurations keeps the
 // program in a basic block of its own, where it rounds as it does in
-// qcd_kernel.  Events 0 .. nb - 1 from the pointers on, whose rows are n apart.
+// qcd_kernel.
 template <class Proc, typename T, int E>
 __global__ void __launch_bounds__(kBlock)
 qcd_sub_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t nb, int64_t n, int nhel,
@@ -704,10 +705,10 @@ __device__ __forceinline__ void kpoly_outputs(const double* B, const qcd_launch&
 // One event per lane (processes with fewer than 64 helicity configurations).
 template <class Proc, typename T>
 __global__ void __launch_bounds__(kBlock)
-qcd_kpoly_lane_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t n, qcd_launch a,
-                      double* __restrict__ out, double* __restrict__ me0_out) {
+qcd_kpoly_lane_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t nb, int64_t n,
+                      qcd_launch a, double* __restrict__ out, double* __restrict__ me0_out) {
     const int64_t e = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (e >= n) return;
+    if (e >= nb) return;
     double p[Proc::NEXT][4];
     load_event<Proc::NEXT>(mom, n, e, p);
     typename Proc::template kin<T> k;
@@ -793,14 +794,13 @@ __global__ void rescue_reset_kernel(unsigned long long* count) {
     if (blockIdx.x == 0 && threadIdx.x == 0) count[0] = 0;
 }
 
-// Events e0 .. e0 + nb - 1 of the n in mom.
+// Events 0 .. nb - 1 from mom on, whose rows are n apart.
 template <class Proc>
 __global__ void __launch_bounds__(kBlock)
-rescue_flag_kernel(const double* __restrict__ mom, int64_t n, int64_t e0, int64_t nb, double tau,
+rescue_flag_kernel(const double* __restrict__ mom, int64_t n, int64_t nb, double tau,
                    unsigned long long* __restrict__ count, int64_t* __restrict__ list) {
-    const int64_t el = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (el >= nb) return;
-    const int64_t e = e0 + el;
+    const int64_t e = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+    if (e >= nb) return;
     double p[Proc::NEXT][4];
     load_event<Proc::NEXT>(mom, n, e, p);
     if (ill_conditioned<Proc>(p, tau)) list[atomicAdd(count, 1ull)] = e;
@@ -944,46 +944,6 @@ qcd_redo_kernel(const double* __restrict__ mom, const int64_t* __restrict__ list
 
 constexpr unsigned kRescueBlocks = 1024;
 
-// The FP64 re-evaluation after a one-event-per-lane pass: list the
-// ill-conditioned events, then redo them.  With a scratch span the count and
-// list live there and the events are flagged and redone chunk by chunk.
-template <class Proc>
-hipError_t launch_rescue(const double* mom, const double* w_in, int64_t n, const qcd_launch& a, double* out,
-                         double* me0, hipStream_t s) {
-    if constexpr (Proc::NEXT <= 4) {
-        return hipSuccess;   // no final-state gluon
-    } else {
-        int64_t* buf = nullptr;
-        int64_t chunk = n;
-        if (a.scratch.ptr) {
-            chunk = scratch_chunk(a.scratch, sizeof(int64_t), 256);
-            if (chunk < 1) return hipErrorInvalidValue;
-            buf = static_cast<int64_t*>(a.scratch.ptr);
-        } else {
-            hipError_t err = work_alloc(reinterpret_cast<void**>(&buf), sizeof(int64_t) * size_t(n + 1), s);
-            if (err != hipSuccess) return err;
-        }
-        unsigned long long* count = reinterpret_cast<unsigned long long*>(buf);
-        int64_t* list = a.scratch.ptr ? buf + 32 : buf + 1;   // after the 256-byte head in a scratch span
-        hipError_t err = hipSuccess;
-        for (int64_t e0 = 0; e0 < n && err == hipSuccess; e0 += chunk) {
-            const int64_t nb = n - e0 < chunk ? n - e0 : chunk;
-            hipLaunchKernelGGL((rescue_reset_kernel<Proc>), dim3(1), dim3(64), 0, s, count);
-            hipLaunchKernelGGL((rescue_flag_kernel<Proc>), dim3(unsigned((nb + kBlock - 1) / kBlock)), dim3(kBlock),
-                               0, s, mom, n, e0, nb, a.rescue_tau, count, list);
-            if (a.kpoly)
-                hipLaunchKernelGGL((qcd_rescue_kpoly_kernel<Proc>), dim3(kRescueBlocks), dim3(kBlock), 0, s, mom,
-                                   list, count, w_in, n, a, out, me0);
-            else
-                hipLaunchKernelGGL((qcd_rescue_kernel<Proc>), dim3(kRescueBlocks), dim3(kBlock), 0, s, mom, list,
-                                   count, w_in, n, int(Proc::NHEL), a, out, me0);
-            err = hipGetLastError();
-        }
-        hipError_t ferr = a.scratch.ptr ? hipSuccess : hipFreeAsync(buf, s);
-        return err != hipSuccess ? err : ferr;
-    }
-}
-
 // |M|^2 of events e0 .. e0 + nb - 1 from their records, M points a pass, then
 // (list non-null) of the listed ones again in double precision.
 template <class Proc, typename T, int M>
@@ -1078,20 +1038,6 @@ hipError_t launch_wave_pipeline(const double* mom, const double* w_in, int64_t n
     if (a.scratch.ptr) return err;
     hipError_t ferr = hipFreeAsync(mem, s);
     return err != hipSuccess ? err : ferr;
-}
-
-template <class Proc, typename T>
-hipError_t launch_kpoly(const double* mom, const double* w_in, int64_t n, const qcd_launch& a, double* out,
-                        double* me0, hipStream_t s) {
-    if constexpr (Proc::NHEL % 64 == 0) {
-        return launch_wave_pipeline<Proc, T, true>(mom, w_in, n, a, out, me0, s);
-    } else {
-        mark(a.t0, s);
-        hipLaunchKernelGGL((qcd_kpoly_lane_kernel<Proc, T>), dim3(unsigned((n + kBlock - 1) / kBlock)), dim3(kBlock),
-                           0, s, mom, w_in, n, a, out, me0);
-        mark(a.t1, s);
-        return hipGetLastError();
-    }
 }
 
 // ------------------------------------------- programs split over kernels
@@ -1673,17 +1619,6 @@ hipError_t launch_split(const split_launchers<Proc>& L, int fp64, const double* 
     return err != hipSuccess ? err : ferr;
 }
 
-// Launch the reweight (mode 0) or single-point (mode 1) kernels of Proc at the
-// requested arithmetic; returns the launch status.
-template <class Proc, typename T>
-hipError_t launch_wave(const double* mom, const double* w_in, int64_t n, const qcd_launch& a, double* out,
-                       double* me0, hipStream_t s) {
-    if constexpr (Proc::NHEL % 64 != 0)
-        return hipErrorInvalidConfiguration;
-    else
-        return launch_wave_pipeline<Proc, T, false>(mom, w_in, n, a, out, me0, s);
-}
-
 // Events of a workgroup of qcd_sub_kernel: 32, so that few lanes wait for the
 // kinematics, where that still fills the 768 workgroups that run at once
 // several times; below, what the workgroup's lanes hold at once.
@@ -1697,58 +1632,119 @@ constexpr int64_t kSubEvents = 196608;
 constexpr int64_t lane_events(int fp64) { return fp64 ? 106496 : 126976; }
 // A launch holds kLaunchBlocks E events: 2^29 of g g -> t tbar g.
 template <class Proc, int E>
-void launch_sub(int fp64, const double* mom, const double* w_in, int64_t n, const qcd_launch& a, double* out,
-                double* me0, hipStream_t s) {
+void launch_sub(int fp64, const double* mom, const double* w_in, int64_t nb, int64_t n, const qcd_launch& a,
+                double* out, double* me0, hipStream_t s) {
     const auto kernel = fp64 ? qcd_sub_kernel<Proc, double, E> : qcd_sub_kernel<Proc, float, E>;
-    for (int64_t e0 = 0; e0 < n; e0 += kLaunchBlocks * E) {
-        const int64_t nb = n - e0 < kLaunchBlocks * E ? n - e0 : kLaunchBlocks * E;
-        hipLaunchKernelGGL(kernel, dim3(unsigned((nb + E - 1) / E)), dim3(kBlock), 0, s, mom + e0,
-                           w_in ? w_in + e0 : nullptr, nb, n, int(Proc::NHEL), a, out + e0, me0 ? me0 + e0 : nullptr);
+    for (int64_t e0 = 0; e0 < nb; e0 += kLaunchBlocks * E) {
+        const int64_t m = nb - e0 < kLaunchBlocks * E ? nb - e0 : kLaunchBlocks * E;
+        hipLaunchKernelGGL(kernel, dim3(unsigned((m + E - 1) / E)), dim3(kBlock), 0, s, mom + e0,
+                           w_in ? w_in + e0 : nullptr, m, n, int(Proc::NHEL), a, out + e0, me0 ? me0 + e0 : nullptr);
     }
 }
 
+// Events 0 .. nb - 1 from the pointers on, whose rows are n apart: one per lane
+// or several per wave.
 template <class Proc>
-hipError_t launch_main(int fp64, const double* mom, const double* w_in, int64_t n, const qcd_launch& a,
-                       double* out, double* me0, hipStream_t s) {
-    if (a.kpoly)
-        return fp64 ? launch_kpoly<Proc, double>(mom, w_in, n, a, out, me0, s)
-                    : launch_kpoly<Proc, float>(mom, w_in, n, a, out, me0, s);
-    if (a.mapping == MGRW_MAP_EVENT_PER_WAVE)
-        return fp64 ? launch_wave<Proc, double>(mom, w_in, n, a, out, me0, s)
-                    : launch_wave<Proc, float>(mom, w_in, n, a, out, me0, s);
+hipError_t launch_lane_kernels(int fp64, const double* mom, const double* w_in, int64_t nb, int64_t n,
+                               const qcd_launch& a, double* out, double* me0, hipStream_t s) {
+    const dim3 grid(unsigned((nb + kBlock - 1) / kBlock));
+    if (a.kpoly) {
+        if constexpr (Proc::NHEL % 64 != 0)
+            hipLaunchKernelGGL((fp64 ? qcd_kpoly_lane_kernel<Proc, double> : qcd_kpoly_lane_kernel<Proc, float>), grid,
+                               dim3(kBlock), 0, s, mom, w_in, nb, n, a, out, me0);
+        return hipGetLastError();
+    }
     if constexpr (Proc::NHEL < 64) {
         if (a.mapping == MGRW_MAP_AUTO && !(Proc::NG <= 2 && a.batch >= lane_events(fp64))) {
             constexpr int G = kBlock / Proc::NHEL;   // events a workgroup's lanes hold at once
-            mark(a.t0, s);
             if (a.batch >= kSubEvents)
-                launch_sub<Proc, kSubTile>(fp64, mom, w_in, n, a, out, me0, s);
+                launch_sub<Proc, kSubTile>(fp64, mom, w_in, nb, n, a, out, me0, s);
             else
-                launch_sub<Proc, G>(fp64, mom, w_in, n, a, out, me0, s);
-            mark(a.t1, s);
+                launch_sub<Proc, G>(fp64, mom, w_in, nb, n, a, out, me0, s);
             return hipGetLastError();
         }
     }
     constexpr int NBD = lane_block<Proc, double>(), NBF = lane_block<Proc, float>();
-    mark(a.t0, s);
     if (fp64)
-        hipLaunchKernelGGL((qcd_kernel<Proc, double>), dim3(unsigned((n + NBD - 1) / NBD)), dim3(NBD), 0, s, mom, w_in,
-                           n, a, out, me0);
+        hipLaunchKernelGGL((qcd_kernel<Proc, double>), dim3(unsigned((nb + NBD - 1) / NBD)), dim3(NBD), 0, s, mom,
+                           w_in, nb, n, a, out, me0);
     else
-        hipLaunchKernelGGL((qcd_kernel<Proc, float>), dim3(unsigned((n + NBF - 1) / NBF)), dim3(NBF), 0, s, mom, w_in,
-                           n, a, out, me0);
-    mark(a.t1, s);
+        hipLaunchKernelGGL((qcd_kernel<Proc, float>), dim3(unsigned((nb + NBF - 1) / NBF)), dim3(NBF), 0, s, mom,
+                           w_in, nb, n, a, out, me0);
     return hipGetLastError();
+}
+
+// The kernels that write weights directly, then the FP64 re-evaluation of the
+// ill-conditioned events, which reads the input weights a second time: where
+// the outputs overlap them they are set aside first.  Buffers: count, list,
+// weights.  With a scratch span the events run in chunks whose buffers fit.
+template <class Proc>
+hipError_t launch_lanes(int fp64, const double* mom, const double* w_in, int64_t n, const qcd_launch& a, double* out,
+                        double* me0, hipStream_t s) {
+    const bool rescue = !fp64 && a.rescue_tau > 0.0 && Proc::NEXT > 4;   // there is a final-state gluon
+    const bool aside =
+        rescue && a.mode == 0 && (overlap(w_in, n, out, (a.npts - 1) * n) || overlap(w_in, n, me0, n));
+    const size_t words = aside ? 2 : 1;
+    int64_t chunk = n;
+    char* mem = nullptr;
+    if (rescue && a.scratch.ptr) {
+        mem = static_cast<char*>(a.scratch.ptr);
+        chunk = scratch_chunk(a.scratch, words * 8, 768);
+        if (chunk < 1) return hipErrorInvalidValue;
+        if (chunk > n) chunk = n;
+    } else if (rescue) {
+        hipError_t err = work_alloc(reinterpret_cast<void**>(&mem), 256 + words * align256(8 * size_t(n)), s);
+        if (err != hipSuccess) return err;
+    }
+    unsigned long long* count = reinterpret_cast<unsigned long long*>(mem);
+    int64_t* list = rescue ? reinterpret_cast<int64_t*>(mem + 256) : nullptr;
+    double* w_buf = aside ? reinterpret_cast<double*>(mem + 256 + align256(8 * size_t(chunk))) : nullptr;
+    hipError_t err = hipSuccess;
+    for (int64_t e0 = 0; e0 < n && err == hipSuccess; e0 += chunk) {
+        const int64_t nb = n - e0 < chunk ? n - e0 : chunk;
+        const unsigned blocks = unsigned((nb + kBlock - 1) / kBlock);
+        const double *p = mom + e0, *w = w_in ? w_in + e0 : nullptr;
+        double *o = out + e0, *m0 = me0 ? me0 + e0 : nullptr;
+        if (aside) {
+            hipLaunchKernelGGL((copy_weights_kernel<kBlock>), dim3(blocks), dim3(kBlock), 0, s, w, nb, w_buf);
+            w = w_buf;
+        }
+        mark(a.t0, s);
+        err = launch_lane_kernels<Proc>(fp64, p, w, nb, n, a, o, m0, s);
+        mark(a.t1, s);
+        if constexpr (Proc::NEXT > 4) {
+            if (!rescue || err != hipSuccess) continue;
+            hipLaunchKernelGGL((rescue_reset_kernel<Proc>), dim3(1), dim3(64), 0, s, count);
+            hipLaunchKernelGGL((rescue_flag_kernel<Proc>), dim3(blocks), dim3(kBlock), 0, s, p, n, nb, a.rescue_tau,
+                               count, list);
+            if (a.kpoly)
+                hipLaunchKernelGGL((qcd_rescue_kpoly_kernel<Proc>), dim3(kRescueBlocks), dim3(kBlock), 0, s, p, list,
+                                   count, w, n, a, o, m0);
+            else
+                hipLaunchKernelGGL((qcd_rescue_kernel<Proc>), dim3(kRescueBlocks), dim3(kBlock), 0, s, p, list, count,
+                                   w, n, int(Proc::NHEL), a, o, m0);
+            err = hipGetLastError();
+        }
+    }
+    if (!mem || a.scratch.ptr) return err;
+    hipError_t ferr = hipFreeAsync(mem, s);
+    return err != hipSuccess ? err : ferr;
 }
 
 template <class Proc>
 hipError_t launch_qcd(int fp64, const double* mom, const double* w_in, int64_t n, const qcd_launch& a,
                       double* out, double* me0, hipStream_t s) {
-    hipError_t err = launch_main<Proc>(fp64, mom, w_in, n, a, out, me0, s);
-    if (err != hipSuccess || fp64 || !(a.rescue_tau > 0.0)) return err;
-    // the one-event-per-wave pipelines re-evaluate their listed events themselves
-    const bool wave = a.kpoly ? Proc::NHEL % 64 == 0 : a.mapping == MGRW_MAP_EVENT_PER_WAVE;
-    if (wave) return err;
-    return launch_rescue<Proc>(mom, w_in, n, a, out, me0, s);
+    if constexpr (Proc::NHEL % 64 == 0) {
+        if (a.kpoly)
+            return fp64 ? launch_wave_pipeline<Proc, double, true>(mom, w_in, n, a, out, me0, s)
+                        : launch_wave_pipeline<Proc, float, true>(mom, w_in, n, a, out, me0, s);
+        if (a.mapping == MGRW_MAP_EVENT_PER_WAVE)
+            return fp64 ? launch_wave_pipeline<Proc, double, false>(mom, w_in, n, a, out, me0, s)
+                        : launch_wave_pipeline<Proc, float, false>(mom, w_in, n, a, out, me0, s);
+    } else if (!a.kpoly && a.mapping == MGRW_MAP_EVENT_PER_WAVE) {
+        return hipErrorInvalidConfiguration;
+    }
+    return launch_lanes<Proc>(fp64, mom, w_in, n, a, out, me0, s);
 }
 
 }  // namespace mgrw
