@@ -32,8 +32,10 @@
  *    into `stream` with events, so the call stays ordered on `stream`.
  *  - Intermediate buffers are stream-ordered allocations from a memory pool of
  *    the library's own (one per device), which keeps up to 12 GiB across
- *    synchronisations and gives its memory back when the last process handle is
- *    destroyed; under stream capture they come from the default pool.
+ *    synchronisations while a process handle is open.  With the last handle it
+ *    gives its memory back, that of calls still running at the next
+ *    synchronisation.  Under stream capture the buffers come from the default
+ *    pool.
  *  - Return values are mgrw_status codes; on a non-OK status the calling
  *    thread's mgrw_last_error() describes it.  No exception crosses the ABI.
  *  - A process handle is not thread-safe; distinct handles are independent.

@@ -5,8 +5,10 @@
 // the program waits for the GPU, and the next call maps its gigabytes again: a
 // g g -> t tbar g g g call of 6001 events x 17 points took 836 ms after each
 // synchronisation against 92 ms without.  This pool keeps up to kPoolKeep
-// bytes across synchronisations; the last handle to be destroyed gives them
-// back.  Allocations and releases are stream-ordered, from any thread, as with
+// bytes across synchronisations while a handle is open.  The last one to be
+// destroyed gives back what is free and, since its last calls may still be
+// running, sets the bytes to keep to 0, so that the next synchronisation
+// returns the rest.  Allocations and releases are stream-ordered, from any thread, as with
 // the default pool.
 #pragma once
 
@@ -37,25 +39,32 @@ struct work_pools {
             props.location.type = hipMemLocationTypeDevice;
             props.location.id = dev;
             hipMemPool_t p = nullptr;
-            uint64_t keep = kPoolKeep;
             if (hipMemPoolCreate(&p, &props) != hipSuccess) {
                 (void)hipGetLastError();
                 return nullptr;
             }
-            if (hipMemPoolSetAttribute(p, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) (void)hipGetLastError();
+            keep(p, kPoolKeep);
             pool[dev] = p;
         }
         return pool[dev];
     }
     void handle_created() {
         std::lock_guard<std::mutex> lock(mu);
-        ++handles;
+        if (handles++ > 0) return;
+        for (hipMemPool_t p : pool)
+            if (p) keep(p, kPoolKeep);
     }
     void handle_destroyed() {
         std::lock_guard<std::mutex> lock(mu);
         if (--handles > 0) return;
-        for (hipMemPool_t p : pool)
-            if (p && hipMemPoolTrimTo(p, 0) != hipSuccess) (void)hipGetLastError();
+        for (hipMemPool_t p : pool) {
+            if (!p) continue;
+            keep(p, 0);
+            if (hipMemPoolTrimTo(p, 0) != hipSuccess) (void)hipGetLastError();
+        }
+    }
+    static void keep(hipMemPool_t p, uint64_t bytes) {
+        if (hipMemPoolSetAttribute(p, hipMemPoolAttrReleaseThreshold, &bytes) != hipSuccess) (void)hipGetLastError();
     }
 };
 inline work_pools& pools() {
