@@ -27,10 +27,15 @@ struct work_pools {
     hipMemPool_t pool[kDevices] = {};
     long handles = 0;
 
-    // The pool of the current device; null where there is none.
-    hipMemPool_t of_device() {
+    // The pool of the stream's device (the current one for the default stream);
+    // null where there is none.
+    hipMemPool_t of_stream(hipStream_t s) {
         int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return nullptr;
+        if (!s || hipStreamGetDevice(s, &dev) != hipSuccess) {
+            (void)hipGetLastError();
+            if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+        }
+        if (dev < 0 || dev >= kDevices) return nullptr;
         std::lock_guard<std::mutex> lock(mu);
         if (!pool[dev]) {
             hipMemPoolProps props = {};
@@ -81,7 +86,7 @@ inline hipError_t work_alloc(void** ptr, size_t bytes, hipStream_t s) {
         (void)hipGetLastError();
         capture = hipStreamCaptureStatusActive;
     }
-    hipMemPool_t p = capture == hipStreamCaptureStatusNone ? pools().of_device() : nullptr;
+    hipMemPool_t p = capture == hipStreamCaptureStatusNone ? pools().of_stream(s) : nullptr;
     if (p) {
         const hipError_t err = hipMallocFromPoolAsync(ptr, bytes, p, s);
         if (err == hipSuccess) return err;

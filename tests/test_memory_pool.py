@@ -119,6 +119,15 @@ CASES = {
     synchronize();
     NEED(used[0] == 500);
     """,
+    # a stream of another device than the current one
+    "device of the stream": """
+    pools().handle_created();
+    NEED(work_alloc(&a, 600, &s1) == hipSuccess);
+    NEED(used[0] == 0 && used[1] == 600);
+    void* b = nullptr;
+    NEED(work_alloc(&b, 500, nullptr) == hipSuccess);
+    NEED(used[0] == 500 && used[1] == 600);
+    """,
 }
 
 
