@@ -31,10 +31,11 @@ struct work_pools {
     // null where there is none.
     hipMemPool_t of_stream(hipStream_t s) {
         int dev = -1;
-        if (!s || hipStreamGetDevice(s, &dev) != hipSuccess) {
+        if (s && hipStreamGetDevice(s, &dev) != hipSuccess) {
             (void)hipGetLastError();
-            if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+            s = nullptr;
         }
+        if (!s && hipGetDevice(&dev) != hipSuccess) return nullptr;
         if (dev < 0 || dev >= kDevices) return nullptr;
         std::lock_guard<std::mutex> lock(mu);
         if (!pool[dev]) {
@@ -88,7 +89,12 @@ inline hipError_t work_alloc(void** ptr, size_t bytes, hipStream_t s) {
     }
     hipMemPool_t p = capture == hipStreamCaptureStatusNone ? pools().of_stream(s) : nullptr;
     if (p) {
-        const hipError_t err = hipMallocFromPoolAsync(ptr, bytes, p, s);
+        hipError_t err = hipMallocFromPoolAsync(ptr, bytes, p, s);
+        if (err == hipSuccess) return err;
+        (void)hipGetLastError();
+        // what the pool keeps may be what is missing
+        if (hipMemPoolTrimTo(p, 0) != hipSuccess) (void)hipGetLastError();
+        err = hipMallocFromPoolAsync(ptr, bytes, p, s);
         if (err == hipSuccess) return err;
         (void)hipGetLastError();   // the default pool may still have room
     }

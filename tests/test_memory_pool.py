@@ -56,7 +56,7 @@ inline hipError_t hipMemPoolTrimTo(hipMemPool_t p, size_t keep) {
     return hipSuccess;
 }
 inline hipError_t hipMallocFromPoolAsync(void** ptr, size_t bytes, hipMemPool_t p, hipStream_t) {
-    const size_t reuse = p->held < bytes ? p->held : bytes;
+    const size_t reuse = bytes <= p->held ? bytes : 0;   // a larger one is a new block
     if (used[p->dev] - reuse + bytes > room) return hipErrorOutOfMemory;
     used[p->dev] += bytes - reuse;
     p->held -= reuse;
@@ -118,6 +118,13 @@ CASES = {
     NEED(work_alloc(&a, 500, &s0) == hipSuccess && hipFreeAsync(a, &s0) == hipSuccess);
     synchronize();
     NEED(used[0] == 500);
+    """,
+    # what the pool keeps is in the way of a larger buffer
+    "kept memory makes room": """
+    pools().handle_created();
+    NEED(work_alloc(&a, 600, &s0) == hipSuccess && hipFreeAsync(a, &s0) == hipSuccess);
+    synchronize();
+    NEED(work_alloc(&a, 700, &s0) == hipSuccess && used[0] == 700);
     """,
     # a stream of another device than the current one
     "device of the stream": """
