@@ -442,6 +442,7 @@ template <typename T> struct shared_root : std::false_type {};
 template <> struct shared_root<double> : std::true_type {};
 template <typename T, int M, bool S = shared_root<T>::value>
 struct ttk {
+    static_assert(M <= 2, "MGRW_CLOSE_V3 and MGRW_CLOSE_V4 close two points of a single-precision pass");
     v4<T> v[M];
 };
 template <typename T, int M>
