@@ -16,6 +16,7 @@
 
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 
 namespace mgrw {
 
@@ -74,8 +75,10 @@ struct work_pools {
     }
 };
 inline work_pools& pools() {
-    static work_pools* p = new work_pools;   // never destroyed: handles may outlive static objects
-    return *p;
+    // never destroyed (handles may outlive static objects) and nothing that throws
+    static_assert(std::is_trivially_destructible<work_pools>::value, "no destructor at exit");
+    static work_pools p;
+    return p;
 }
 
 // Stream-ordered allocation for a launch on stream s, released with
