@@ -849,50 +849,59 @@ qcd_rescue_kpoly_kernel(const double* __restrict__ mom, const int64_t* __restric
     }
 }
 
-// The same after the kernels that write weights directly: one workgroup per
-// listed event, its points dealt to groups of as many lanes as there are
-// helicity configurations (at most 64), so that all lanes work and a short
-// list's latency is that of a few points.  g g -> t tbar g, 300 events x 17
-// points: 180 -> 99 us; one wave per event, half of its lanes idle, took the
-// points one by one.
+// The same after the kernels that write weights directly: a workgroup deals the
+// points of its listed events to groups of as many lanes as there are helicity
+// configurations (at most 64), so that all lanes work and a short list's
+// latency is that of a few points.  Lists longer than the grid go several
+// events at a time, whose kinematics are formed side by side and whose points
+// fill the groups also where there are fewer points than groups.  g g -> t tbar
+// g: 300 events x 17 points 180 -> 99 us against one wave per event, half of
+// its lanes idle, points one by one; 1.5 10^6 events, 2 % of them listed, at one point 862 ->
+// 290 us of re-evaluation (one event at a time left seven of eight groups idle;
+// one wave per event: 262), two points 755 -> 246.
+constexpr int kRedoEvents = 8;
 template <class Proc>
 __global__ void __launch_bounds__(kBlock, 1)
 qcd_rescue_kernel(const double* __restrict__ mom, const int64_t* __restrict__ list,
                   const unsigned long long* __restrict__ count, const double* __restrict__ w_in, int64_t n, int nhel,
                   qcd_launch a, double* __restrict__ out, double* __restrict__ me0_out) {
     constexpr int L = Proc::NHEL < 64 ? Proc::NHEL : 64;
-    __shared__ typename Proc::template kin<double> k;
-    __shared__ typename Proc::template basis<double> b;
-    __shared__ double mes[kMaxLaunchPoints];
+    __shared__ typename Proc::template kin<double> k[kRedoEvents];
+    __shared__ typename Proc::template basis<double> b[kRedoEvents];
+    __shared__ double mes[kRedoEvents * kMaxLaunchPoints];
     const int64_t cnt = int64_t(count[0]);
+    const int64_t share = (cnt + gridDim.x - 1) / gridDim.x;
+    const int per = share < kRedoEvents ? int(share) : kRedoEvents;
     const int sub = threadIdx.x % L;
 #pragma unroll 1
-    for (int64_t i = blockIdx.x; i < cnt; i += gridDim.x) {   // the same for the whole workgroup
-        const int64_t e = list[i];
-        if (threadIdx.x == 0) {
+    for (int64_t i0 = int64_t(blockIdx.x) * per; i0 < cnt; i0 += int64_t(gridDim.x) * per) {   // whole workgroup
+        const int m = cnt - i0 < per ? int(cnt - i0) : per;
+        if (threadIdx.x < m) {
             double p[Proc::NEXT][4];
-            load_event<Proc::NEXT>(mom, n, e, p);
-            Proc::kinematics(p, a.mt, k);
-            Proc::external_basis(p, a.mt, b);
+            load_event<Proc::NEXT>(mom, n, list[i0 + threadIdx.x], p);
+            Proc::kinematics(p, a.mt, k[threadIdx.x]);
+            Proc::external_basis(p, a.mt, b[threadIdx.x]);
         }
         __syncthreads();
 #pragma unroll 1
-        for (int kp = threadIdx.x / L; kp < a.npts; kp += kBlock / L) {
-            const qcd_point pt = a.pts[kp];
-            const double me = group_sum<L>(helicities_me<Proc, double>(k, b, pt, sub, L, nhel));
-            if (sub == 0) mes[kp] = me * Proc::point_norm(pt.gs);
+        for (int u = threadIdx.x / L; u < m * a.npts; u += kBlock / L) {
+            const int i = u / a.npts;
+            const qcd_point pt = a.pts[u - i * a.npts];
+            const double me = group_sum<L>(helicities_me<Proc, double>(k[i], b[i], pt, sub, L, nhel));
+            if (sub == 0) mes[u] = me * Proc::point_norm(pt.gs);
         }
         __syncthreads();
-        const int kp = threadIdx.x;
-        if (kp < a.npts) {
+        for (int u = threadIdx.x; u < m * a.npts; u += kBlock) {
+            const int i = u / a.npts, kp = u - i * a.npts;
+            const int64_t e = list[i0 + i];
             if (kp > 0)
-                out[int64_t(kp - 1) * n + e] = reweighted(w_in ? w_in[e] : 1.0, mes[kp], mes[0]);
+                out[int64_t(kp - 1) * n + e] = reweighted(w_in ? w_in[e] : 1.0, mes[u], mes[i * a.npts]);
             else if (a.mode == 1)
-                out[e] = mes[0];
+                out[e] = mes[u];
             else if (me0_out)
-                me0_out[e] = mes[0];
+                me0_out[e] = mes[u];
         }
-        __syncthreads();   // the next event overwrites the shared data
+        __syncthreads();   // the next events overwrite the shared data
     }
 }
 
