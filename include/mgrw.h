@@ -131,9 +131,10 @@ mgrw_status mgrw_eval_me(mgrw_process *p, const double *mom, int64_t n_events, i
  * float64[n_events], may be NULL) receives |M_base|^2.  Momenta are read once
  * for all points; chains that hold no parameter are formed once for several
  * points, couplings, flows, colour and helicity sums at every point.
- * g g -> t tbar: the number of events selects one of two kernels (see
- * MGRW_OPT_LANE_MAPPING), which agree to double rounding; for every other
- * process an event's result does not depend on the batch it is in.
+ * g g -> t tbar and g g -> t tbar g: the numbers of events and points select
+ * one of two kernels (see MGRW_OPT_LANE_MAPPING), which agree to double
+ * rounding; for every other process an event's result does not depend on the
+ * batch it is in.
  * Weights in place: w_in may be a row of w_out or be me_base_out (here, in
  * mgrw_reweight_noalloc and in mgrw_reweight_kpoly); the arrays must not
  * overlap in any other way.
@@ -195,8 +196,8 @@ mgrw_status mgrw_process_info(const mgrw_process *p, int *n_ext, int *n_flows, i
 
 /* Options.  MGRW_OPT_LANE_MAPPING selects how events map onto the GPU's
  * lanes for the exact QCD kernels: MGRW_MAP_AUTO (default:
- * several events per wave where the configurations do not fill one, else one
- * per wave; large g g -> t tbar batches one per lane),
+ * one event per wave where the configurations fill one, else several per wave
+ * or one per lane, whichever is faster for the numbers of events and points),
  * MGRW_MAP_EVENT_PER_LANE (one event per lane, helicities in a loop), or
  * MGRW_MAP_EVENT_PER_WAVE (one event per 64-lane wave, helicity
  * configurations on the lanes; processes with a multiple of 64 helicity

@@ -186,7 +186,7 @@ mgrw_status run(mgrw_process* p, const double* mom, const double* w_in, int64_t 
     a.mode = mode;
     a.mt = p->base.mt;
     // automatic choice: one event per wave when the helicity configurations fill
-    // whole waves; the others choose by the batch (launch_lane_kernels)
+    // whole waves; the others choose by events and points (lanes_faster)
     a.mapping = p->mapping != MGRW_MAP_AUTO ? p->mapping
                 : (info_of(p->proc).n_hel % 64 == 0 ? MGRW_MAP_EVENT_PER_WAVE : MGRW_MAP_AUTO);
     a.batch = whole > 0 ? whole : n;

@@ -45,7 +45,7 @@ struct qcd_launch {
     int npts;        // points in pts (base first)
     int mode;        // 0: reweight, 1: |M|^2 of pts[0] only
     double mt;
-    int mapping;     // MGRW_MAP_EVENT_PER_LANE or MGRW_MAP_EVENT_PER_WAVE; MGRW_MAP_AUTO: chosen by `batch`
+    int mapping;     // MGRW_MAP_EVENT_PER_LANE or MGRW_MAP_EVENT_PER_WAVE; MGRW_MAP_AUTO: see lanes_faster
     int64_t batch;   // events of the whole call (the launch may be a piece of it)
     int kpoly;       // 1: kappa-polynomial evaluation (one program per helicity for all points)
     double rescue_tau;   // > 0: events with a gluon invariant |2 p_i.p_j|/s below it are redone in FP64
@@ -174,11 +174,10 @@ constexpr int lane_block() {
     }
 }
 
-// One event per lane (large g g -> t tbar batches, or on request).  In single
-// precision the per-lane kinematics and
-// wavefunction bases live in LDS (each lane owns a slot; no barriers); in
-// double precision they stay in registers.  Events 0 .. nb - 1 from the
-// pointers on, whose rows are n apart.
+// One event per lane (where lanes_faster says so, or on request).  In single
+// precision the per-lane kinematics and wavefunction bases live in LDS (each
+// lane owns a slot; no barriers); in double precision they stay in registers.
+// Events 0 .. nb - 1 from the pointers on, whose rows are n apart.
 template <class Proc, typename T>
 __global__ void __launch_bounds__((lane_block<Proc, T>()))
 qcd_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t nb, int64_t n, qcd_launch a,
@@ -1630,15 +1629,46 @@ hipError_t launch_split(const split_launchers<Proc>& L, int fp64, const double* 
 
 // Events of a workgroup of qcd_sub_kernel: 32, so that few lanes wait for the
 // kinematics, where that still fills the 768 workgroups that run at once
-// several times; below, what the workgroup's lanes hold at once.
+// several times; below, what the workgroup's lanes hold at once.  Few points
+// leave the kinematics more weight: g g -> t tbar g, mixed, 65536 events at one
+// point 85 us against 126, at six 418 against 459; at 17, 75000 events, 1419
+// against 1339, equal from 200000 on.
 constexpr int kSubTile = 32;
-constexpr int64_t kSubEvents = 196608;
-// Events from which on g g -> t tbar, whose 385 operations per configuration
-// weigh little against a cross-lane sum per point, runs one event per lane:
-// 2^20 events 2.07 ms against 2.27, in double precision 500000 events 1.70
-// against 1.97; below, a round of that kernel's waves is not full (100000
-// events: 303 us against 239).
-constexpr int64_t lane_events(int fp64) { return fp64 ? 106496 : 126976; }
+constexpr bool sub_tiles(int64_t batch, int npts) { return batch >= (npts <= 8 ? 65536 : 196608); }
+// Whether a batch of a process with fewer than 64 configurations runs one event
+// per lane: from both kernels' times, in us and fitted to 0.9-1.1 of what they
+// measure at 30000 to 1.5 10^6 events and 1 to 65 points.  A lane's time goes
+// in steps, as its kernel adds a wave to every SIMD (g g -> t tbar g in single
+// precision: fills the CUs' LDS, seven waves each): first + step points for
+// every `events` of the batch, the first of them at least `least` steps.  Several events per
+// wave take sub0 + sub1 points ns per event.  For example, times in us of one
+// event per lane and of several per wave (both with this rule's tiles):
+//   g g -> t tbar, mixed   1 point  95000 events  23.4  22.4   115000  23.3  26.8
+//                         17 points 115000 events 303   276    300000  692   675
+//   g g -> t tbar, FP64    1 point  55000 events  19.1  27.4   140000  43.4  52.6
+//                         17 points 65000 events  247   274    105000  450   441
+//   g g -> t tbar g, FP64  1 point  65536 events  140   165    75000   274   205
+//                         17 points 65536 events  2274  2408   150000  6992  5536
+// and g g -> t tbar g in single precision one per lane only for large batches
+// at one point (1.5 10^6 events: 1787 against 1865).
+struct lane_cost {
+    int64_t events;
+    double least, first, step;
+    double sub0, sub1, tile0, tile1;   // per workgroup's lanes, and with tiles
+};
+template <class Proc>
+bool lanes_faster(int fp64, int64_t batch, int npts) {
+    constexpr lane_cost tt[2] = {{65536, 1.85, 5, 8.55, 0.115, 0.132, 0.045, 0.136},
+                                 {65536, 1.08, 5, 13.0, 0.200, 0.235, 0.106, 0.238}};
+    constexpr lane_cost ttg[2] = {{114688, 1, 8, 129, 0.88, 1.015, 0.20, 1.03},
+                                  {65536, 1, 6, 134, 1.455, 2.083, 0.30, 2.133}};
+    static_assert(Proc::NG == 2 || Proc::NG == 3, "measured for g g -> t tbar and g g -> t tbar g");
+    const lane_cost& c = Proc::NG == 2 ? tt[fp64 != 0] : ttg[fp64 != 0];
+    const double steps = double((batch + c.events - 1) / c.events);
+    const double lanes = c.first + c.step * npts * (steps > c.least ? steps : c.least);
+    const double per_event = sub_tiles(batch, npts) ? c.tile0 + c.tile1 * npts : c.sub0 + c.sub1 * npts;
+    return lanes <= 5.0 + 1e-3 * double(batch) * per_event;
+}
 // A launch holds kLaunchBlocks E events: 2^29 of g g -> t tbar g.
 template <class Proc, int E>
 void launch_sub(int fp64, const double* mom, const double* w_in, int64_t nb, int64_t n, const qcd_launch& a,
@@ -1664,9 +1694,9 @@ hipError_t launch_lane_kernels(int fp64, const double* mom, const double* w_in, 
         return hipGetLastError();
     }
     if constexpr (Proc::NHEL < 64) {
-        if (a.mapping == MGRW_MAP_AUTO && !(Proc::NG <= 2 && a.batch >= lane_events(fp64))) {
+        if (a.mapping == MGRW_MAP_AUTO && !lanes_faster<Proc>(fp64, a.batch, a.npts)) {
             constexpr int G = kBlock / Proc::NHEL;   // events a workgroup's lanes hold at once
-            if (a.batch >= kSubEvents)
+            if (sub_tiles(a.batch, a.npts))
                 launch_sub<Proc, kSubTile>(fp64, mom, w_in, nb, n, a, out, me0, s);
             else
                 launch_sub<Proc, G>(fp64, mom, w_in, nb, n, a, out, me0, s);
