@@ -1634,7 +1634,7 @@ hipError_t launch_split(const split_launchers<Proc>& L, int fp64, const double* 
 // point 85 us against 126, at six 418 against 459; at 17, 75000 events, 1419
 // against 1339, equal from 200000 on.
 constexpr int kSubTile = 32;
-constexpr bool sub_tiles(int64_t batch, int npts) { return batch >= (npts <= 8 ? 65536 : 196608); }
+constexpr bool sub_tiles(int64_t n, int npts) { return n >= (npts <= 8 ? 65536 : 196608); }
 // Whether a batch of a process with fewer than 64 configurations runs one event
 // per lane: from both kernels' times, in us and fitted to 0.9-1.1 of what they
 // measure at 30000 to 1.5 10^6 events and 1 to 65 points.  A lane's time goes
@@ -1696,7 +1696,7 @@ hipError_t launch_lane_kernels(int fp64, const double* mom, const double* w_in, 
     if constexpr (Proc::NHEL < 64) {
         if (a.mapping == MGRW_MAP_AUTO && !lanes_faster<Proc>(fp64, a.batch, a.npts)) {
             constexpr int G = kBlock / Proc::NHEL;   // events a workgroup's lanes hold at once
-            if (sub_tiles(a.batch, a.npts))
+            if (sub_tiles(nb, a.npts))   // the same weights, whichever
                 launch_sub<Proc, kSubTile>(fp64, mom, w_in, nb, n, a, out, me0, s);
             else
                 launch_sub<Proc, G>(fp64, mom, w_in, nb, n, a, out, me0, s);
