@@ -148,7 +148,7 @@ mgrw_status mgrw_reweight(mgrw_process *p, const double *mom, const double *w_in
  * per-event kinematics records and the list of events for the FP64
  * re-evaluation come from a 256 MiB device array inside the library (one per
  * GPU, held until the process ends); the events run in chunks whose buffers
- * fit it (about 1e5 events per chunk for g g -> t tbar g g).  The call
+ * fit it (about 1.1e5 events per chunk for g g -> t tbar g g).  The call
  * allocates nothing and records no kernel timing (mgrw_kernel_time_ms then
  * reports MGRW_ERR_STATE).  Every call on a GPU shares that GPU's array, so
  * calls that overlap on one GPU (other streams, other threads, other handles)

@@ -297,36 +297,49 @@ __device__ __forceinline__ bool ill_conditioned(const double (&p)[Proc::NEXT][4]
     return ill;
 }
 
+// An event's record: its kinematics and what its consumer makes the external
+// wavefunctions from, their table (the kernels that stage the record in LDS) or
+// their bases.  With both a g g -> t tbar g g record is 16 % larger.
 template <class Proc, typename T>
-struct event_data {
+struct table_record {
     typename Proc::template kin<T> k;
-    typename Proc::template basis<T> b;
     typename Proc::template ext_table<T> t;
     int skip;   // 1: left to the FP64 re-evaluation
+    template <typename P>
+    __device__ __forceinline__ void fill(const P& p, double mt) {
+        typename Proc::template basis<T> b;
+        Proc::kinematics(p, mt, k);
+        Proc::external_basis(p, mt, b);
+        Proc::external_table(b, t);
+    }
 };
-
-template <class Proc, typename T, typename P>
-__device__ __forceinline__ void fill_event(const P& p, double mt, event_data<Proc, T>& d) {
-    Proc::kinematics(p, mt, d.k);
-    Proc::external_basis(p, mt, d.b);
-    Proc::external_table(d.b, d.t);
-}
+template <class Proc, typename T>
+struct basis_record {
+    typename Proc::template kin<T> k;
+    typename Proc::template basis<T> b;
+    int skip;
+    template <typename P>
+    __device__ __forceinline__ void fill(const P& p, double mt) {
+        Proc::kinematics(p, mt, k);
+        Proc::external_basis(p, mt, b);
+    }
+};
 
 // Kinematics and wavefunction bases of every event; with tau > 0 also lists
 // the ill-conditioned events (count, list) and marks them to be skipped.
 // Events e0 .. e0 + nb - 1 of the n in mom; record el holds event e0 + el and
 // the list holds event numbers.
-template <class Proc, typename T>
+template <class Proc, class Record>
 __global__ void __launch_bounds__(kBlock)
 qcd_setup_kernel(const double* __restrict__ mom, int64_t n, int64_t e0, int64_t nb, double mt,
-                 event_data<Proc, T>* __restrict__ ev, double tau, unsigned long long* __restrict__ count,
+                 Record* __restrict__ ev, double tau, unsigned long long* __restrict__ count,
                  int64_t* __restrict__ list) {
     const int64_t el = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     if (el >= nb) return;
     const int64_t e = e0 + el;
     double p[Proc::NEXT][4];
     load_event<Proc::NEXT>(mom, n, e, p);
-    fill_event(p, mt, ev[el]);
+    ev[el].fill(p, mt);
     int skip = 0;
     if (tau > 0.0 && ill_conditioned<Proc>(p, tau)) {
         skip = 1;
@@ -654,7 +667,7 @@ constexpr int64_t kWholeEvents = 16384;
 // SIMD (256 registers) are needed and one runs at half rate.
 template <class Proc, typename T, int M>
 __global__ void __launch_bounds__(kBlock, sizeof(T) == 4 ? MGRW_WAVE_WPE : 1)
-qcd_wave_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t nb, int64_t n, int units, int per,
+qcd_wave_kernel(const table_record<Proc, T>* __restrict__ ev, int64_t e0, int64_t nb, int64_t n, int units, int per,
                 qcd_launch a, double* __restrict__ out, double* __restrict__ me0) {
     static_assert(Proc::NHEL % 64 == 0, "helicity configurations must fill whole waves");
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -741,7 +754,7 @@ constexpr bool kpoly_lds_split() {
 // One event per wave, helicity configurations on the lanes.
 template <class Proc, typename T>
 __global__ void __launch_bounds__(kBlock)
-qcd_kpoly_wave_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t nb,
+qcd_kpoly_wave_kernel(const basis_record<Proc, T>* __restrict__ ev, int64_t e0, int64_t nb,
                       const double* __restrict__ w_in, int64_t n, qcd_launch a, double* __restrict__ out,
                       double* __restrict__ me0_out) {
     const int64_t el = int64_t(blockIdx.x) * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -955,7 +968,7 @@ constexpr unsigned kRescueBlocks = 1024;
 // |M|^2 of events e0 .. e0 + nb - 1 from their records, M points a pass, then
 // (list non-null) of the listed ones again in double precision.
 template <class Proc, typename T, int M>
-void launch_passes(const event_data<Proc, T>* ev, const double* mom, int64_t n, int64_t e0, int64_t nb,
+void launch_passes(const table_record<Proc, T>* ev, const double* mom, int64_t n, int64_t e0, int64_t nb,
                    const int64_t* list, const unsigned long long* count, const qcd_launch& a, double* out,
                    double* me0, hipStream_t s) {
     const int passes = (a.npts + M - 1) / M;
@@ -983,7 +996,7 @@ hipError_t launch_wave_pipeline(const double* mom, const double* w_in, int64_t n
                                 double* me0, hipStream_t s) {
     const bool rescue = sizeof(T) == 4 && a.rescue_tau > 0.0 && Proc::NEXT > 4;
     const bool base = !KP && a.mode == 0 && !me0;   // room for |M|^2 at the base point
-    using ED = event_data<Proc, T>;
+    using ED = std::conditional_t<KP, basis_record<Proc, T>, table_record<Proc, T>>;
     // room for the input weights, where the outputs overlap them
     const bool aside = !KP && a.mode == 0 && (overlap(w_in, n, out, (a.npts - 1) * n) || overlap(w_in, n, me0, n));
     const size_t words = (rescue ? 1 : 0) + (base ? 1 : 0) + (aside ? 1 : 0);
@@ -1014,7 +1027,7 @@ hipError_t launch_wave_pipeline(const double* mom, const double* w_in, int64_t n
     for (int64_t e0 = 0; e0 < n && err == hipSuccess; e0 += chunk) {
         const int64_t nb = n - e0 < chunk ? n - e0 : chunk;
         if (rescue) hipLaunchKernelGGL((rescue_reset_kernel<Proc>), dim3(1), dim3(64), 0, s, count);
-        hipLaunchKernelGGL((qcd_setup_kernel<Proc, T>), dim3(unsigned((nb + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+        hipLaunchKernelGGL((qcd_setup_kernel<Proc, ED>), dim3(unsigned((nb + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                            s, mom, n, e0, nb, a.mt, ev, rescue ? a.rescue_tau : 0.0, count, list);
         if constexpr (KP) {
             mark(a.t0, s);
@@ -1075,7 +1088,7 @@ struct mfma_colour<P, std::void_t<decltype(P::MFMA_COLOUR)>> : std::bool_constan
 // One wave's unit of work: points [u per, (u + 1) per) of one event.
 template <class Proc, typename T, int C, bool STORE_LAST>
 __global__ void __launch_bounds__(kBlock, MGRW_PART_WPE)
-qcd_part_kernel(const event_data<Proc, T>* __restrict__ ev, int64_t e0, int64_t nb, T* __restrict__ jbuf, int64_t n,
+qcd_part_kernel(const basis_record<Proc, T>* __restrict__ ev, int64_t e0, int64_t nb, T* __restrict__ jbuf, int64_t n,
                 int units, int per, qcd_launch a, double* __restrict__ out, double* __restrict__ me0) {
     constexpr int NH = Proc::NHEL, K2 = 2 * Proc::K;
     constexpr bool LAST = C + 1 == Proc::NCHUNK && !STORE_LAST;   // finishes the events here
@@ -1144,7 +1157,7 @@ int split_units(int64_t nb, int npts) {
 }
 
 template <class Proc, typename T, int C>
-hipError_t launch_part(const event_data<Proc, T>* ev, int64_t e0, int64_t nb, T* jbuf, int64_t n, const qcd_launch& a,
+hipError_t launch_part(const basis_record<Proc, T>* ev, int64_t e0, int64_t nb, T* jbuf, int64_t n, const qcd_launch& a,
                        double* out, double* me0, hipStream_t s) {
     const int units = split_units<C>(nb, a.npts), per = a.npts / units;
     const dim3 grid(unsigned((nb * units + kBlock / 64 - 1) / (kBlock / 64)));
@@ -1299,13 +1312,13 @@ template <class Proc>
 __global__ void __launch_bounds__(kBlock)
 qcd_setup64_kernel(const double* __restrict__ mom, int64_t n, double mt, const int64_t* __restrict__ list,
                    const unsigned long long* __restrict__ count, int64_t slots,
-                   event_data<Proc, double>* __restrict__ ev) {
+                   table_record<Proc, double>* __restrict__ ev) {
     const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     if (i >= slots || (count && i >= int64_t(count[0]))) return;
     const int64_t e = list ? list[i] : i;
     double p[Proc::NEXT][4];
     load_event<Proc::NEXT>(mom, n, e, p);
-    fill_event(p, mt, ev[i]);
+    ev[i].fill(p, mt);
     ev[i].skip = 0;
 }
 
@@ -1350,7 +1363,7 @@ __host__ __device__ inline int split64_points(int npts) {
 }
 template <class Proc, int C, int R, int M>
 __global__ void __launch_bounds__(kBlock, 1)
-qcd_fr_kernel(const event_data<Proc, double>* __restrict__ ev, const unsigned long long* __restrict__ count,
+qcd_fr_kernel(const table_record<Proc, double>* __restrict__ ev, const unsigned long long* __restrict__ count,
               int64_t e0, int64_t nb, double* __restrict__ jbuf, qcd_launch a) {
     constexpr int NH = Proc::NHEL, K2 = 2 * Proc::K, KR = Proc::KR;
     static_assert(NH % 64 == 0, "helicity configurations must fill whole waves");
@@ -1432,7 +1445,7 @@ qcd_colour64_kernel(const double* __restrict__ jbuf, const int64_t* __restrict__
 }
 
 template <class Proc, int C, int R>
-hipError_t launch_fr(const event_data<Proc, double>* ev, const unsigned long long* count, int64_t e0, int64_t nb,
+hipError_t launch_fr(const table_record<Proc, double>* ev, const unsigned long long* count, int64_t e0, int64_t nb,
                      double* jbuf, const qcd_launch& a, hipStream_t s) {
     const int64_t passes = a.npts > 1 ? (a.npts + kPointsSplit64 - 1) / kPointsSplit64 : 1;
     const dim3 grid(unsigned((nb * passes + kBlock / 64 - 1) / (kBlock / 64)));
@@ -1447,9 +1460,9 @@ hipError_t launch_fr(const event_data<Proc, double>* ev, const unsigned long lon
 // Kernel launchers of a split program, one translation unit each.
 template <class Proc>
 struct split_launchers {
-    using part_fn = hipError_t (*)(const event_data<Proc, float>*, int64_t, int64_t, float*, int64_t,
+    using part_fn = hipError_t (*)(const basis_record<Proc, float>*, int64_t, int64_t, float*, int64_t,
                                    const qcd_launch&, double*, double*, hipStream_t);
-    using fr_fn = hipError_t (*)(const event_data<Proc, double>*, const unsigned long long*, int64_t, int64_t,
+    using fr_fn = hipError_t (*)(const table_record<Proc, double>*, const unsigned long long*, int64_t, int64_t,
                                  double*, const qcd_launch&, hipStream_t);
     part_fn part[Proc::NCHUNK];
     fr_fn fr[Proc::NCHUNK64 * Proc::NFR];
@@ -1477,7 +1490,7 @@ template <class Proc>
 hipError_t launch_split64(const split_launchers<Proc>& L, const double* mom, int64_t n, const int64_t* list,
                           const unsigned long long* count, int64_t slots, const qcd_launch& a, double* out,
                           double* me0, hipStream_t s, bool timed) {
-    using ED = event_data<Proc, double>;
+    using ED = table_record<Proc, double>;
     const int jpts = split64_points(a.npts);
     const int64_t B = part_batch<Proc, double>(slots, jpts);
     ED* ev = nullptr;
@@ -1560,7 +1573,7 @@ template <class Proc>
 hipError_t launch_split_me(const split_launchers<Proc>& L, int fp64, const double* mom, int64_t n, const qcd_launch& a,
                            double* out, double* me0, hipStream_t s) {
     if (fp64) return launch_split64<Proc>(L, mom, n, nullptr, nullptr, n, a, out, me0, s, true);
-    using ED = event_data<Proc, float>;
+    using ED = basis_record<Proc, float>;
     const bool rescue = a.rescue_tau > 0.0;
     const int64_t B = part_batch<Proc, float>(n, a.npts);
     ED* ev = nullptr;
@@ -1580,7 +1593,7 @@ hipError_t launch_split_me(const split_launchers<Proc>& L, int fp64, const doubl
     unsigned long long* count = rescue ? reinterpret_cast<unsigned long long*>(buf) : nullptr;
     int64_t* list = rescue ? buf + 1 : nullptr;
     if (rescue) hipLaunchKernelGGL((rescue_reset_kernel<Proc>), dim3(1), dim3(64), 0, s, count);
-    hipLaunchKernelGGL((qcd_setup_kernel<Proc, float>), dim3(unsigned((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL((qcd_setup_kernel<Proc, ED>), dim3(unsigned((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
                        mom, n, int64_t(0), n, a.mt, ev, rescue ? a.rescue_tau : 0.0, count, list);
     err = hipGetLastError();
     mark(a.t0, s);

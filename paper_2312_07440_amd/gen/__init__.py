@@ -52,9 +52,9 @@ def generate(outdir=None, procs=None, force=False):
             body = (f"hipError_t launch_{name}{sig} {{\n"
                     f"    return launch_qcd<{name}>(fp64, mom, w_in, n, a, out, me0, s);\n}}\n")
         else:
-            psig = (f"(const event_data<{name}, float>* ev, int64_t e0, int64_t nb, float* jbuf,\n"
+            psig = (f"(const basis_record<{name}, float>* ev, int64_t e0, int64_t nb, float* jbuf,\n"
                     "    int64_t n, const qcd_launch& a, double* out, double* me0, hipStream_t s)")
-            fsig = (f"(const event_data<{name}, double>* ev, const unsigned long long* count, int64_t e0,\n"
+            fsig = (f"(const table_record<{name}, double>* ev, const unsigned long long* count, int64_t e0,\n"
                     "    int64_t nb, double* jbuf, const qcd_launch& a, hipStream_t s)")
             for c in range(nch):
                 put(os.path.join(outdir, f"qcd_{name}_part{c}.hip"),

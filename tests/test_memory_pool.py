@@ -187,3 +187,37 @@ def test_memory_comes_back():
     r = subprocess.run([sys.executable, "-c", ON_GPU], cwd=ROOT, capture_output=True, text=True, timeout=110)
     print(r.stdout, r.stderr[-2000:], flush=True)
     assert r.returncode == 0
+
+
+HELD = """
+import sys, torch
+import paper_2312_07440_amd as mg
+from synth import generate_events
+n = 1 << 20
+mom = torch.from_numpy(generate_events("gg_ttgg", 4096)).cuda().repeat(1, 1, n // 4096).contiguous()
+out = torch.empty((1, n), dtype=torch.float64, device="cuda")
+def call(p, k):
+    p.set_params([{"kappa_ttg": 1.1}])
+    getattr(p, sys.argv[1])(mom[:, :, :k].contiguous(), out=out[:, :k])
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+with torch.no_grad():
+    call(mg.Process("gg_ttgg", "mixed"), 64)     # code objects
+    a = torch.cuda.mem_get_info()[0]
+    p = mg.Process("gg_ttgg", "mixed")
+    call(p, n)
+    print((a - torch.cuda.mem_get_info()[0]) / n)
+"""
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call,need", [("reweight", 1984 + 352 + 8), ("reweight_kpoly", 1984 + 160 + 4)])
+def test_bytes_per_event(call, need):
+    """What a g g -> t tbar g g call holds per event: the record's kinematics
+    and the wavefunctions' table or bases, whichever the call reads, a list
+    entry, the base |M|^2, and up to 64 MiB that allocations are rounded up by."""
+    r = subprocess.run([sys.executable, "-c", HELD, call], cwd=ROOT, capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0, r.stderr[-2000:]
+    held = float(r.stdout.split()[-1])
+    print(call, held, "bytes per event", flush=True)
+    assert need <= held <= need + 16 + 64
