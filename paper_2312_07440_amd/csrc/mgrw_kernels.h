@@ -1,5 +1,6 @@
-// Kernel templates of libmgrw (one event per lane) and the per-process
-// launcher, shared by the per-process translation units.
+// Kernel templates of libmgrw's QCD processes (one event per lane, several per
+// wave, one per wave, programs split over kernels) and their launchers, shared
+// by the per-process translation units.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -213,7 +214,7 @@ qcd_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int6
 // lane, whose slots in LDS allow seven waves per CU: g g -> t tbar g, base + 16
 // points, mixed (150 registers, three waves per SIMD), 262147 events 6.80 ->
 // 4.84 ms, 10^6 events 20.5 -> 18.4; and 5000 events, which are 79 waves of the
-// other kernel, 2.03 -> 0.23 ms.
+// other kernel, 2.03 -> 0.15 ms with the re-evaluation.
 // nhel = NHEL, as an argument: the loop over a lane's configurations keeps the
 // program in a basic block of its own, where it rounds as it does in
 // qcd_kernel.
@@ -266,9 +267,11 @@ qcd_sub_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, 
 // ------------------------------------------------ one event per wave
 //
 // Lanes carry helicity configurations (h = lane + 64 c); the event's
-// kinematics and wavefunction bases are wave-uniform, computed once per event
-// by qcd_setup_kernel and read through the scalar cache, so they occupy
-// neither vector registers nor LDS.  The helicity sum is a wave reduction.
+// kinematics and wavefunctions are wave-uniform, computed once per event by
+// qcd_setup_kernel.  The plain kernels and the split programs' in double
+// precision stage that record in LDS, one copy per wave; the kappa-polynomial
+// kernel and the single-precision parts read it through the scalar cache.  The
+// helicity sum is a wave reduction.
 
 #ifndef MGRW_WAVE_WPE
 #define MGRW_WAVE_WPE 2
@@ -656,9 +659,12 @@ inline bool overlap(const double* a, int64_t na, const double* b, int64_t nb) {
 
 // Events from which on a unit of work is a whole event; below, one pass, so
 // that a small batch fills the chip (2048 waves in single precision, 1024 in
-// double).  1000 events x 17 points: 305 us against 1150 with whole events;
-// at 33000 events units of one pass still gain 1 %, at 65536 and above whole
-// events, which stage their record once, are 2-4 % faster.
+// double).  1000 events x 17 points: 305 us against 1150 with whole events.  Once
+// whole events fill the chip (2048 events) they are faster, as they stage their
+// record once: by 1-4 % in single precision at 3, 5, 17 and 65 points, by 3-8 % in
+// double at 5 and more; units of one pass are faster where few whole events are
+// left for the last round (9000 events in single precision: 1-7 %; 33000: 0.3 %
+// at 17 points), the less so the more rounds there are: eight at 16384.
 constexpr int64_t kWholeEvents = 16384;
 
 // One wave's unit of work: event e0 + el, passes [u per, (u + 1) per) over its
@@ -779,8 +785,8 @@ qcd_kpoly_wave_kernel(const basis_record<Proc, T>* __restrict__ ev, int64_t e0, 
             kpoly_colour<Proc, T>(J, B);
         } else if constexpr (sizeof(T) == 8) {
             // double precision: external wavefunctions in the lane's own LDS
-            // slot, as in qcd_wave_kernel (10 % faster for g g -> t tbar g g;
-            // in single precision registers are faster)
+            // slot (10 % faster for g g -> t tbar g g; in single precision
+            // registers are faster)
             __shared__ lds_slot<typename Proc::template ext<T>> wfs[kBlock];
             kpoly_helicity<Proc, T>(ev[el].k, ev[el].b, hc + lane, B, wfs[threadIdx.x].v);
         } else {
@@ -1070,9 +1076,10 @@ hipError_t launch_wave_pipeline(const double* mom, const double* w_in, int64_t n
 // between the parts through HBM in a [event][point][component][helicity]
 // layout, the helicities in blocks of 64 (consecutive lanes touch consecutive
 // words, and one pass's flows are one contiguous piece).  By default the last
-// part forms the colour sum (VALU), the helicity sum (wave reduction) and the
-// reweighted weights; with the matrix-core colour sum selected it stores J
-// too, and qcd_colour_mfma_kernel contracts J with the colour matrix.
+// part forms the colour sum (VALU) and the helicity sum (wave reduction), which
+// is |M|^2; with the matrix-core colour sum selected it stores J too, and
+// qcd_colour_mfma_kernel contracts J with the colour matrix.
+// reweight_ratio_kernel forms the weights, after the FP64 re-evaluation.
 
 // Processes whose generated struct provides the bfloat16 split of the colour
 // matrix (MFMA_COLOUR) take the matrix-core colour sum.
@@ -1301,7 +1308,7 @@ hipError_t launch_colour_mfma(const float* jbuf, int64_t e0, int64_t nb, int64_t
 // events, one event per wave with the helicity configurations on the lanes,
 // and passes the range's amplitudes through HBM ([event][point][component]
 // [helicity], as the single-precision parts do); qcd_colour64_kernel then
-// forms the colour sum from HBM, the helicity sum and the weights.
+// forms the colour sum from HBM and the helicity sum, which is |M|^2.
 //
 // The same pipeline re-evaluates the ill-conditioned events of the
 // single-precision pass: slots are then positions in the list of those

@@ -8,8 +8,10 @@
 // bytes across synchronisations while a handle is open.  The last one to be
 // destroyed gives back what is free and, since its last calls may still be
 // running, sets the bytes to keep to 0, so that the next synchronisation
-// returns the rest.  Allocations and releases are stream-ordered, from any thread, as with
-// the default pool.
+// returns the rest.  What a call needs beyond kPoolKeep (from 5.4 10^6 events of
+// g g -> t tbar g g in single precision on, whose records are one buffer) still
+// goes back at every synchronisation.  Allocations and releases are
+// stream-ordered, from any thread, as with the default pool.
 #pragma once
 
 #include <hip/hip_runtime.h>
