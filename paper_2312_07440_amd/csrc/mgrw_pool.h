@@ -10,8 +10,9 @@
 // running, sets the bytes to keep to 0, so that the next synchronisation
 // returns the rest.  What a call needs beyond kPoolKeep (from 5.4 10^6 events of
 // g g -> t tbar g g in single precision on, whose records are one buffer) still
-// goes back at every synchronisation.  Allocations and releases are
-// stream-ordered, from any thread, as with the default pool.
+// goes back at every synchronisation (2^23 events x 2 points, 20 GB: 193.8 ms
+// each when the GPU is waited for after every call, 192.9 queued).  Allocations
+// and releases are stream-ordered, from any thread, as with the default pool.
 #pragma once
 
 #include <hip/hip_runtime.h>

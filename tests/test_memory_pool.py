@@ -155,7 +155,7 @@ def test_pool(name, tmp_path):
 
 
 ON_GPU = """
-import torch
+import time, torch
 import paper_2312_07440_amd as mg
 from synth import generate_events
 mom = torch.from_numpy(generate_events("gg_ttggg", 2000, first_event=5)).cuda()
@@ -167,6 +167,7 @@ def call():
     return p
 def free():
     torch.cuda.synchronize()
+    time.sleep(0.5)              # released memory is counted as free with some delay
     return torch.cuda.mem_get_info()[0]
 call().close()
 a = free()                       # code objects and streams are there from now on
