@@ -181,8 +181,8 @@ constexpr int lane_block() {
 // Events 0 .. nb - 1 from the pointers on, whose rows are n apart.
 template <class Proc, typename T>
 __global__ void __launch_bounds__((lane_block<Proc, T>()))
-qcd_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t nb, int64_t n, qcd_launch a,
-           double* __restrict__ out, double* __restrict__ me0_out) {
+qcd_kernel(const double* __restrict__ mom, const double* __restrict__ w_in, int64_t n, qcd_launch a,
+           double* __restrict__ out, double* __restrict__ me0_out, int64_t nb) {
     constexpr int NB = lane_block<Proc, T>();
     const int64_t e = int64_t(blockIdx.x) * NB + threadIdx.x;
     if (e >= nb) return;   // no barriers below: early exit is safe
@@ -1678,7 +1678,7 @@ struct lane_cost {
 };
 template <class Proc>
 bool lanes_faster(int fp64, int64_t batch, int npts) {
-    constexpr lane_cost tt[2] = {{65536, 1.85, 5, 8.55, 0.115, 0.132, 0.045, 0.136},
+    constexpr lane_cost tt[2] = {{65536, 1.85, 5, 8.50, 0.115, 0.132, 0.050, 0.137},
                                  {65536, 1.08, 5, 13.0, 0.200, 0.235, 0.106, 0.238}};
     constexpr lane_cost ttg[2] = {{114688, 1, 8, 129, 0.88, 1.015, 0.20, 1.03},
                                   {65536, 1, 6, 134, 1.455, 2.083, 0.30, 2.133}};
@@ -1726,10 +1726,10 @@ hipError_t launch_lane_kernels(int fp64, const double* mom, const double* w_in, 
     constexpr int NBD = lane_block<Proc, double>(), NBF = lane_block<Proc, float>();
     if (fp64)
         hipLaunchKernelGGL((qcd_kernel<Proc, double>), dim3(unsigned((nb + NBD - 1) / NBD)), dim3(NBD), 0, s, mom,
-                           w_in, nb, n, a, out, me0);
+                           w_in, n, a, out, me0, nb);
     else
         hipLaunchKernelGGL((qcd_kernel<Proc, float>), dim3(unsigned((nb + NBF - 1) / NBF)), dim3(NBF), 0, s, mom,
-                           w_in, nb, n, a, out, me0);
+                           w_in, n, a, out, me0, nb);
     return hipGetLastError();
 }
 
